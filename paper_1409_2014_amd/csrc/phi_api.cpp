@@ -95,27 +95,38 @@ struct Layout {
     }
 };
 // everything a plan reads and never writes
+struct NodeParts {
+    Part q, cell, sub, cst, con, taps;
+};
 struct TableParts {
-    Part deconv, gx, gy, gyr, q, cell, sub, cst, con, taps, twr, twn;
+    Part deconv, gx, gy, gyr, twr, twn;
+    NodeParts half, all;
 };
 // everything a solve writes
 struct WorkParts {
     Part xt, tt, win, pts, tiles, u;
 };
 
+NodeParts layout_nodes(const phi::NodeSet& ns, size_t es, Layout& L) {
+    NodeParts t;
+    t.q = L.take(ns.q.size() * 8);
+    t.cell = L.take(ns.cell.size() * 4);
+    t.sub = L.take(ns.sub.size() * 4);
+    t.cst = L.take(ns.contrib_start.size() * 4);
+    t.con = L.take(ns.contrib.size() * 4);
+    t.taps = L.take(ns.taps.size() * es);
+    return t;
+}
+
 TableParts layout_tables(const phi::HostPlan& hp, size_t es, Layout& L) {
     TableParts t;
-    const size_t n = hp.n, f = hp.n_fine, m = hp.n_nodes;
+    const size_t n = hp.n, f = hp.n_fine;
     t.deconv = L.take(n * 8);
     t.gx = L.take(2 * (f / 2 + 1) * 8);
     t.gy = L.take(2 * f * 8);
     t.gyr = L.take(2 * f * es);
-    t.q = L.take(m * 8);
-    t.cell = L.take(hp.cell.size() * 4);
-    t.sub = L.take(hp.sub.size() * 4);
-    t.cst = L.take(hp.contrib_start.size() * 4);
-    t.con = L.take(hp.contrib.size() * 4);
-    t.taps = L.take(hp.taps.size() * es);
+    t.half = layout_nodes(hp.half, es, L);
+    t.all = layout_nodes(hp, es, L);
     t.twr = L.take(hp.twr.size() * es);
     t.twn = L.take(hp.twn.size() * es);
     return t;
@@ -158,12 +169,16 @@ hipError_t upload_tables(const phi::HostPlan& hp, const TableParts& t, char* bas
     if (e == hipSuccess) e = up(t.gx, hp.gx.data());
     if (e == hipSuccess) e = up(t.gy, hp.gy.data());
     if (e == hipSuccess) e = up(t.gyr, narrow(hp.gy));
-    if (e == hipSuccess) e = up(t.q, hp.q.data());
-    if (e == hipSuccess) e = up(t.cell, hp.cell.data());
-    if (e == hipSuccess) e = up(t.sub, hp.sub.data());
-    if (e == hipSuccess) e = up(t.cst, hp.contrib_start.data());
-    if (e == hipSuccess) e = up(t.con, hp.contrib.data());
-    if (e == hipSuccess) e = up(t.taps, narrow(hp.taps));
+    auto up_nodes = [&](const NodeParts& np, const phi::NodeSet& ns) {
+        if (e == hipSuccess) e = up(np.q, ns.q.data());
+        if (e == hipSuccess) e = up(np.cell, ns.cell.data());
+        if (e == hipSuccess) e = up(np.sub, ns.sub.data());
+        if (e == hipSuccess) e = up(np.cst, ns.contrib_start.data());
+        if (e == hipSuccess) e = up(np.con, ns.contrib.data());
+        if (e == hipSuccess) e = up(np.taps, narrow(ns.taps));
+    };
+    up_nodes(t.half, hp.half);
+    up_nodes(t.all, hp);
     const void* twr = hp.twr.data();
     if (f32) {
         keep.emplace_back();
@@ -237,13 +252,21 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
     d->gx = reinterpret_cast<const double*>(base + t.gx.off);
     d->gy = reinterpret_cast<const double*>(base + t.gy.off);
     d->gyr = base + t.gyr.off;
-    d->q = reinterpret_cast<const double*>(base + t.q.off);
-    d->cell = reinterpret_cast<const int*>(base + t.cell.off);
-    d->taps = base + t.taps.off;
-    d->sub = reinterpret_cast<const int*>(base + t.sub.off);
-    d->contrib_start = reinterpret_cast<const int*>(base + t.cst.off);
-    d->contrib = reinterpret_cast<const int*>(base + t.con.off);
-    d->n_sub = hp.n_sub;
+    auto tables = [&](const NodeParts& np, const phi::NodeSet& ns) {
+        phi::NodeTables nt;
+        nt.q = reinterpret_cast<const double*>(base + np.q.off);
+        nt.cell = reinterpret_cast<const int*>(base + np.cell.off);
+        nt.taps = base + np.taps.off;
+        nt.sub = reinterpret_cast<const int*>(base + np.sub.off);
+        nt.contrib_start = reinterpret_cast<const int*>(base + np.cst.off);
+        nt.contrib = reinterpret_cast<const int*>(base + np.con.off);
+        nt.n_sub = ns.n_sub;
+        nt.col_lo = ns.col_lo;
+        nt.col_hi = ns.col_hi;
+        return nt;
+    };
+    d->nd = tables(t.half, hp.half);
+    d->nd_all = tables(t.all, hp);
     d->bin = hp.bin;
     d->tile = hp.tile;
     d->twr = base + t.twr.off;
@@ -428,8 +451,8 @@ bool same_params(const phi_params& a, const phi_params& b) {
 
 // Work items of one member and stage: first row / column / subproblem of each
 // block.  Members are listed largest first, so the last blocks to start are short.
-void push_items(std::vector<phi::WorkItem>* v, int member, int kind, int count, int step) {
-    for (int i = 0; i < count; i += step) v->push_back({member, i, kind, 0});
+void push_items(std::vector<phi::WorkItem>* v, int member, int kind, int from, int to, int step) {
+    for (int i = from; i < to; i += step) v->push_back({member, i, kind, 0});
 }
 
 }  // namespace
@@ -598,11 +621,11 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         for (int i : order) {
             const phi::HostPlan& hp = plan->sets[plan->member_set[i]];
             const int g = phi::batch_lines(hp.log_fine);
-            push_items(&rows, i, 0, hp.n, g);
-            push_items(hp.component == 2 ? &cols_mixed : &cols, i, 0, hp.n_fine / 2 + 1, g);
-            push_items(&cols_t2, i, 1, hp.patch, g);
-            push_items(&nodes, i, 0, hp.n_sub, 1);
-            push_items(&cols1, i, 0, hp.patch, g);
+            push_items(&rows, i, 0, 0, hp.n, g);
+            push_items(hp.component == 2 ? &cols_mixed : &cols, i, 0, 0, hp.n_fine / 2 + 1, g);
+            push_items(&cols_t2, i, 1, hp.half.col_lo, hp.half.col_hi, g);
+            push_items(&nodes, i, 0, 0, hp.half.n_sub, 1);
+            push_items(&cols1, i, 0, hp.half.col_lo, hp.half.col_hi, g);
         }
         // one allocation: table sets, member workspaces, device views, work tables
         Layout L;

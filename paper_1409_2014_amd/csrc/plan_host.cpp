@@ -407,122 +407,158 @@ void polar_nodes(const HostPlan& hp, std::vector<double>* kx, std::vector<double
     }
 }
 
-phi_status build_host_plan(const phi_params* p, HostPlan* hp, std::string* err) {
-    phi_status st = derive(p, hp, err);
-    if (st != PHI_OK) return st;
-    const int n = hp->n, nf = hp->n_fine, w = hp->width;
-    const double half_w = 0.5 * w;
+namespace {
 
-    // ---- polar nodes, first kernel tap, sort by first-tap cell, taps ------------
-    std::vector<double> kx, ky, q;
-    polar_nodes(*hp, &kx, &ky, &q);
-    const int m = hp->n_nodes;
-    const int q_side = hp->patch, lo = hp->patch_lo;
+// Sorts the nodes listed in `pick` (indices into kx, ky, q; weights times
+// `weight`) and builds their subproblems and tile-reduction lists.
+phi_status build_node_set(const HostPlan& hp, const std::vector<double>& kx, const std::vector<double>& ky,
+                          const std::vector<double>& q, const std::vector<int>& pick, double weight,
+                          NodeSet* set, std::string* err) {
+    const int nf = hp.n_fine, w = hp.width;
+    const double half_w = 0.5 * w;
+    const int m = static_cast<int>(pick.size());
+    const int q_side = hp.patch, lo = hp.patch_lo;
     std::vector<double> ux(m), uy(m);
     std::vector<int> cx(m), cy(m);
-    for (int j = 0; j < m; ++j) {
+    for (int i = 0; i < m; ++i) {
         // t_j / Delta with t_j = 2 pi h k_j, Delta = 2 pi / n_fine: node position in cells
-        ux[j] = nf * hp->h * kx[j];
-        uy[j] = nf * hp->h * ky[j];
+        ux[i] = nf * hp.h * kx[pick[i]];
+        uy[i] = nf * hp.h * ky[pick[i]];
         // first tap l0 = ceil(u - w/2), as a window cell (wrapped when the window is
         // the whole periodic fine grid)
-        const int ax = posmod(static_cast<int>(std::ceil(ux[j] - half_w)) - lo, nf);
-        const int ay = posmod(static_cast<int>(std::ceil(uy[j] - half_w)) - lo, nf);
+        const int ax = posmod(static_cast<int>(std::ceil(ux[i] - half_w)) - lo, nf);
+        const int ay = posmod(static_cast<int>(std::ceil(uy[i] - half_w)) - lo, nf);
         if (q_side < nf && (ax + w > q_side || ay + w > q_side)) {
             *err = "internal: node taps outside the fine-grid window";
             return PHI_ERR_INTERNAL;
         }
-        cx[j] = ax;
-        cy[j] = ay;
+        cx[i] = ax;
+        cy[i] = ay;
     }
     // bins of bin x bin window cells; nodes sorted by the bin of their first tap
-    const int bin = hp->bin;
+    const int bin = hp.bin;
     const int nb = q_side / bin;        // the window side is a power of two >= 16
     const bool whole = (q_side == nf);
     std::vector<int> key(m);
-    for (int j = 0; j < m; ++j) key[j] = (cy[j] / bin) * nb + cx[j] / bin;
+    for (int i = 0; i < m; ++i) key[i] = (cy[i] / bin) * nb + cx[i] / bin;
     std::vector<int> order(m);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key[a] < key[b]; });
-    hp->kx.resize(m); hp->ky.resize(m); hp->q.resize(m);
-    hp->cell.resize(2 * static_cast<size_t>(m));
-    hp->taps.resize(static_cast<size_t>(m) * 2 * w);
+    set->kx.resize(m); set->ky.resize(m); set->q.resize(m);
+    set->cell.resize(2 * static_cast<size_t>(m));
+    set->taps.resize(static_cast<size_t>(m) * 2 * w);
     for (int i = 0; i < m; ++i) {
-        const int j = order[i];
-        hp->kx[i] = kx[j]; hp->ky[i] = ky[j]; hp->q[i] = q[j];
-        hp->cell[2 * i] = cx[j];
-        hp->cell[2 * i + 1] = cy[j];
+        const int o = order[i], j = pick[o];
+        set->kx[i] = kx[j]; set->ky[i] = ky[j]; set->q[i] = weight * q[j];
+        set->cell[2 * i] = cx[o];
+        set->cell[2 * i + 1] = cy[o];
         // psi(u - l) for the w taps l = l0 .. l0 + w - 1
-        const double l0x = std::ceil(ux[j] - half_w), l0y = std::ceil(uy[j] - half_w);
+        const double l0x = std::ceil(ux[o] - half_w), l0y = std::ceil(uy[o] - half_w);
         for (int t = 0; t < w; ++t) {
-            const double dx = ux[j] - (l0x + t), dy = uy[j] - (l0y + t);
-            hp->taps[(static_cast<size_t>(i) * 2 + 0) * w + t] =
-                hp->gaussian_kernel ? std::exp(-hp->beta * dx * dx) : es_kernel(dx / half_w, hp->beta);
-            hp->taps[(static_cast<size_t>(i) * 2 + 1) * w + t] =
-                hp->gaussian_kernel ? std::exp(-hp->beta * dy * dy) : es_kernel(dy / half_w, hp->beta);
+            const double dx = ux[o] - (l0x + t), dy = uy[o] - (l0y + t);
+            set->taps[(static_cast<size_t>(i) * 2 + 0) * w + t] =
+                hp.gaussian_kernel ? std::exp(-hp.beta * dx * dx) : es_kernel(dx / half_w, hp.beta);
+            set->taps[(static_cast<size_t>(i) * 2 + 1) * w + t] =
+                hp.gaussian_kernel ? std::exp(-hp.beta * dy * dy) : es_kernel(dy / half_w, hp.beta);
         }
     }
+    // window columns the taps touch (all of them when the window wraps)
+    set->col_lo = 0;
+    set->col_hi = q_side;
+    if (!whole && m > 0) {
+        const auto mm = std::minmax_element(cx.begin(), cx.end());
+        set->col_lo = *mm.first / bin * bin;
+        set->col_hi = std::min(q_side, *mm.second + w);
+    }
     // subproblems: runs of at most sub_nodes nodes of one bin
-    hp->sub.clear();
+    set->sub.clear();
     int max_bin = 0;
     for (int i = 0; i < m;) {
         const int k = key[order[i]];
         int e = i;
         while (e < m && key[order[e]] == k) ++e;
         max_bin = std::max(max_bin, e - i);
-        for (int s0 = i; s0 < e; s0 += hp->sub_nodes) {
-            hp->sub.push_back(k % nb);
-            hp->sub.push_back(k / nb);
-            hp->sub.push_back(s0);
-            hp->sub.push_back(std::min(hp->sub_nodes, e - s0));
+        for (int s0 = i; s0 < e; s0 += hp.sub_nodes) {
+            set->sub.push_back(k % nb);
+            set->sub.push_back(k / nb);
+            set->sub.push_back(s0);
+            set->sub.push_back(std::min(hp.sub_nodes, e - s0));
         }
         i = e;
     }
-    hp->nb = nb;
-    hp->tile = bin + w - 1;
-    hp->n_sub = static_cast<int>(hp->sub.size() / 4);
-    hp->max_cell_nodes = max_bin;
+    set->n_sub = static_cast<int>(set->sub.size() / 4);
+    set->max_cell_nodes = max_bin;
     // window cell <- tile entries: every tile cell inside the box its nodes' taps
-    // can reach, mapped to its window cell (wrapped when the window is periodic)
-    const int E = hp->tile;
-    std::vector<std::pair<int, int>> pairs;   // (window cell, flat tile index)
-    for (int sidx = 0; sidx < hp->n_sub; ++sidx) {
-        const int bx = hp->sub[4 * sidx], by = hp->sub[4 * sidx + 1];
-        const int first = hp->sub[4 * sidx + 2], count = hp->sub[4 * sidx + 3];
-        int ox0 = bin, ox1 = -1, oy0 = bin, oy1 = -1;
-        for (int i = first; i < first + count; ++i) {
-            ox0 = std::min(ox0, hp->cell[2 * i] - bx * bin);
-            ox1 = std::max(ox1, hp->cell[2 * i] - bx * bin);
-            oy0 = std::min(oy0, hp->cell[2 * i + 1] - by * bin);
-            oy1 = std::max(oy1, hp->cell[2 * i + 1] - by * bin);
-        }
-        for (int cb = oy0; cb <= oy1 + w - 1; ++cb) {
-            for (int ca = ox0; ca <= ox1 + w - 1; ++ca) {
-                int wx = bx * bin + ca, wy = by * bin + cb;
-                if (whole) {
-                    wx %= q_side;
-                    wy %= q_side;
-                } else if (wx >= q_side || wy >= q_side) {
-                    continue;
+    // can reach, mapped to its window cell (wrapped when the window is periodic);
+    // the lists are in subproblem order (two passes: count, then place)
+    const int E = hp.tile;
+    auto each_entry = [&](auto&& visit) {
+        for (int sidx = 0; sidx < set->n_sub; ++sidx) {
+            const int bx = set->sub[4 * sidx], by = set->sub[4 * sidx + 1];
+            const int first = set->sub[4 * sidx + 2], count = set->sub[4 * sidx + 3];
+            int ox0 = bin, ox1 = -1, oy0 = bin, oy1 = -1;
+            for (int i = first; i < first + count; ++i) {
+                ox0 = std::min(ox0, set->cell[2 * i] - bx * bin);
+                ox1 = std::max(ox1, set->cell[2 * i] - bx * bin);
+                oy0 = std::min(oy0, set->cell[2 * i + 1] - by * bin);
+                oy1 = std::max(oy1, set->cell[2 * i + 1] - by * bin);
+            }
+            for (int cb = oy0; cb <= oy1 + w - 1; ++cb) {
+                for (int ca = ox0; ca <= ox1 + w - 1; ++ca) {
+                    int wx = bx * bin + ca, wy = by * bin + cb;
+                    if (whole) {
+                        wx %= q_side;
+                        wy %= q_side;
+                    } else if (wx >= q_side || wy >= q_side) {
+                        continue;
+                    }
+                    visit(wx * q_side + wy, sidx * E * E + cb * E + ca);
                 }
-                pairs.emplace_back(wx * q_side + wy, sidx * E * E + cb * E + ca);
             }
         }
-    }
-    std::stable_sort(pairs.begin(), pairs.end(),
-                     [](const std::pair<int, int>& a, const std::pair<int, int>& b) { return a.first < b.first; });
-    hp->contrib_start.assign(static_cast<size_t>(q_side) * q_side + 1, 0);
-    hp->contrib.resize(pairs.size());
-    for (size_t k = 0; k < pairs.size(); ++k) {
-        hp->contrib_start[pairs[k].first + 1] += 1;
-        hp->contrib[k] = pairs[k].second;
-    }
+    };
+    set->contrib_start.assign(static_cast<size_t>(q_side) * q_side + 1, 0);
+    each_entry([&](int cell, int) { set->contrib_start[cell + 1] += 1; });
     int max_gather = 0;
-    for (size_t c = 1; c < hp->contrib_start.size(); ++c) {
-        max_gather = std::max(max_gather, hp->contrib_start[c]);
-        hp->contrib_start[c] += hp->contrib_start[c - 1];
+    for (size_t c = 1; c < set->contrib_start.size(); ++c) {
+        max_gather = std::max(max_gather, set->contrib_start[c]);
+        set->contrib_start[c] += set->contrib_start[c - 1];
     }
-    hp->max_gather = max_gather;
+    set->max_gather = max_gather;
+    set->contrib.resize(set->contrib_start.back());
+    std::vector<int32_t> next(set->contrib_start.begin(), set->contrib_start.end() - 1);
+    each_entry([&](int cell, int entry) { set->contrib[next[cell]++] = entry; });
+    return PHI_OK;
+}
+
+}  // namespace
+
+phi_status build_host_plan(const phi_params* p, HostPlan* hp, std::string* err) {
+    phi_status st = derive(p, hp, err);
+    if (st != PHI_OK) return st;
+    const int n = hp->n, nf = hp->n_fine;
+    const double half_w = 0.5 * hp->width;
+    hp->nb = hp->patch / hp->bin;
+    hp->tile = hp->bin + hp->width - 1;
+
+    // ---- polar nodes: all of them, and the half plane a solve runs on -----------
+    std::vector<double> kx, ky, q;
+    polar_nodes(*hp, &kx, &ky, &q);
+    const int nt = hp->n_theta;
+    std::vector<int> all(hp->n_nodes), half;
+    std::iota(all.begin(), all.end(), 0);
+    half.reserve(all.size() / 2);
+    for (int i = 0; i < hp->n_r; ++i) {
+        for (int j = 0; j < nt / 2; ++j) {
+            // node j and its antipode j + N_theta / 2: the one with kx >= 0
+            const int a = i * nt + j, b = a + nt / 2;
+            half.push_back(kx[a] >= kx[b] ? a : b);
+        }
+    }
+    st = build_node_set(*hp, kx, ky, q, all, 1.0, hp, err);
+    if (st != PHI_OK) return st;
+    st = build_node_set(*hp, kx, ky, q, half, 2.0, &hp->half, err);
+    if (st != PHI_OK) return st;
 
     // ---- deconvolution factors 2 pi / (n_fine psi_hat(n')) ---------------------
     // psi(x) = phi(x / a) with a = (w/2) Delta the kernel half-width in radians:
@@ -531,6 +567,10 @@ phi_status build_host_plan(const phi_params* p, HostPlan* hp, std::string* err) 
     const double a_rad = half_w * 2.0 * kPi / nf;
     for (int i = 0; i < n; ++i) {
         const int np = i - n / 2;
+        if (np > 0) {                      // even in n'
+            hp->deconv[i] = hp->deconv[n - i];
+            continue;
+        }
         double ph;
         if (hp->gaussian_kernel) {
             // psi(x) = exp(-x^2 / (4 tau)) in radians, tau = Delta^2 / (4 beta), has

@@ -24,7 +24,28 @@ constexpr int kBinSize = 4;            // default bin side in fine-grid cells (m
 constexpr int kMaxBinSize = 16;        // largest bin side
 constexpr int kMaxNodesPerSub = 64;    // most nodes per interp / spread subproblem
 
-struct HostPlan {
+// One sorted set of polar nodes with everything the node stage reads: plan
+// order, kernel taps, subproblems and the tile-reduction lists.
+struct NodeSet {
+    std::vector<double> kx, ky, q;      // k_j and q_j of eq. 12 (q without h^2)
+    std::vector<int32_t> cell;          // [2 M] first-tap window cell (x, y), 0 <= c < patch
+    std::vector<double> taps;           // [M][2][w] psi(u_j - l0_j - t), x then y
+    std::vector<int32_t> sub;           // [4 n_sub] bin x, bin y, first node, node count (<= 64)
+    int n_sub = 0;
+    // reduction of the subproblem tiles onto the window: for window cell c = x * patch + y,
+    // entries contrib_start[c] .. contrib_start[c+1]-1 of contrib hold flat tile indices
+    std::vector<int32_t> contrib_start, contrib;
+    int max_cell_nodes = 0;             // most nodes of one bin
+    int max_gather = 0;                 // most tile entries summed into one window cell
+    int col_lo = 0, col_hi = 0;         // window columns x in [col_lo, col_hi) that the nodes' taps touch
+};
+
+// The plan's own set (the base) holds all nodes.  A solve's density is real, so
+// rho_hat(-k) = conj rho_hat(k), and q is even: the nodes of one half plane
+// with twice their weight have the same real part (eq. 12's sum over k and -k).
+// `half` holds that half plane (kx >= 0), which a solve runs on; the type-2 and
+// type-1 stages, whose coefficients belong to every node, run on all of them.
+struct HostPlan : NodeSet {
     // problem
     int n = 0;            // grid side N (even)
     int n_fine = 0;       // FFT side F: the smallest power of two >= kappa N (padded I1 box
@@ -47,20 +68,11 @@ struct HostPlan {
     // fine-grid window touched by the nodes' kernel taps: [patch_lo, patch_lo + patch)
     int patch = 0, patch_lo = 0;
 
-    // node data in plan order: sorted by bin (bin x bin window cells) of the first kernel tap
-    std::vector<double> kx, ky, q;      // k_j and q_j of eq. 12 (q without h^2)
-    std::vector<int32_t> cell;          // [2 M] first-tap window cell (x, y), 0 <= c < patch
-    std::vector<double> taps;           // [M][2][w] psi(u_j - l0_j - t), x then y
+    // node sort: by bin (bin x bin window cells) of the first kernel tap
     int bin = 8, nb = 0;                // bin side in cells, bins per window side
     int sub_nodes = 64;                 // most nodes per subproblem
     int tile = 0;                       // spread tile side E = bin + w - 1
-    std::vector<int32_t> sub;           // [4 n_sub] bin x, bin y, first node, node count (<= 64)
-    int n_sub = 0;
-    // reduction of the subproblem tiles onto the window: for window cell c = x * patch + y,
-    // entries contrib_start[c] .. contrib_start[c+1]-1 of contrib hold flat tile indices
-    std::vector<int32_t> contrib_start, contrib;
-    int max_cell_nodes = 0;             // most nodes of one subproblem's bin
-    int max_gather = 0;                 // most tile entries summed into one window cell
+    NodeSet half;                       // the nodes of the half plane kx >= 0, q doubled
     // tables
     std::vector<double> deconv;         // [N] 2 pi / (n_fine psi_hat(n')), n' = i - N/2
     std::vector<double> gx;             // [2 (F/2+1)] (a, 1 - e^{-a}),  a = kx^2 / sigma^2, kx = m/(n_fine h)

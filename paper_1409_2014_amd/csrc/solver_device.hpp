@@ -121,10 +121,11 @@ __device__ __forceinline__ void rows_forward_body(const DevPlan& P, const R* __r
         if (idx < ITEMS && (EXACT || row0 + gg < n))
             xt[static_cast<size_t>(m) * P.col_stride + row0 + gg] = {R(0.5) * (a.x + b.x), R(0.5) * (a.y - b.y)};
     }
+    // the window columns that the nodes' taps touch
     cpx<R>* tt = static_cast<cpx<R>*>(P.tt);
-    for (int idx = threadIdx.x; idx < P.patch * G; idx += NT * G) {
+    for (int idx = threadIdx.x; idx < (P.nd.col_hi - P.nd.col_lo) * G; idx += NT * G) {
         const int gg = idx % G;
-        const int i = idx / G;
+        const int i = P.nd.col_lo + idx / G;
         const int lf = P.patch_lo + i;
         const cpx<R>* l = lds_all + gg * LP;
         const cpx<R> a = l[lds_pad(lf & (F - 1))];
@@ -305,8 +306,9 @@ __device__ __forceinline__ void cols_type2_body(const DevPlan& P, int i1_base, c
     const cpx<R>* tw = static_cast<const cpx<R>*>(P.twr);
     const int q = P.patch;
     const int i1 = i1_base + g;
-    const bool active = i1 < q;
-    const cpx<R>* col = static_cast<const cpx<R>*>(P.tt) + static_cast<size_t>(active ? i1 : 0) * P.col_stride;
+    const bool active = i1 < P.nd.col_hi;
+    const cpx<R>* col =
+        static_cast<const cpx<R>*>(P.tt) + static_cast<size_t>(active ? i1 : P.nd.col_lo) * P.col_stride;
     const cpx<R> zero = {R(0), R(0)};
     const int half = EXACT ? F / 4 : (P.n >> 1);
     const cpx<R>* base = col + half;
@@ -432,7 +434,7 @@ __device__ __forceinline__ void nodes_body(const DevPlan& P, int sidx, const cpx
                   "small_div covers the tile and tap indices");
     constexpr int TPT = (kMaxNodesPerSub * 2 * WMAX + NTH - 1) / NTH;   // taps per thread
     constexpr int CPT = (kTileMax * kTileMax + NTH - 1) / NTH;                     // tile cells per thread
-    const int* sub = P.sub + 4 * sidx;
+    const int* sub = P.nd.sub + 4 * sidx;
     const int bx = sub[0], by = sub[1], first = sub[2], count = sub[3];
     const int w = W > 0 ? W : P.width;
     const int E = P.tile, q = P.patch, bin = P.bin;
@@ -442,7 +444,7 @@ __device__ __forceinline__ void nodes_body(const DevPlan& P, int sidx, const cpx
     // every global load of the block is issued before the first LDS store, so
     // their latencies overlap: the subproblem's taps (contiguous, w2 per node),
     // the per-node scalars, the type-2 window tile
-    const R* taps = static_cast<const R*>(P.taps) + static_cast<size_t>(first) * w2;
+    const R* taps = static_cast<const R*>(P.nd.taps) + static_cast<size_t>(first) * w2;
     const int n_taps = count * w2;
     R tv[TPT];
 #pragma unroll
@@ -456,9 +458,9 @@ __device__ __forceinline__ void nodes_body(const DevPlan& P, int sidx, const cpx
     double qv = 0.0;
     cpx<R> cv = {R(0), R(0)};
     if (has_node) {
-        cx = P.cell[2 * (first + jn)];
-        cy = P.cell[2 * (first + jn) + 1];
-        if constexpr (MODE == 0) qv = P.q[first + jn];
+        cx = P.nd.cell[2 * (first + jn)];
+        cy = P.nd.cell[2 * (first + jn) + 1];
+        if constexpr (MODE == 0) qv = P.nd.q[first + jn];
         if constexpr (MODE == 2) cv = coef[first + jn];
     }
     cpx<R> tl[CPT];
@@ -644,8 +646,8 @@ __device__ __forceinline__ void cols_type1_body(const DevPlan& P, int i1_base, c
         const int c = e / q;
         const int i2 = e - c * q;
         const int i1 = i1_base + c;
-        const int cell = (i1 < q ? i1 : 0) * q + i2;
-        const int k0 = P.contrib_start[cell], k1 = P.contrib_start[cell + 1];
+        const int cell = (i1 < P.nd.col_hi ? i1 : P.nd.col_lo) * q + i2;
+        const int k0 = P.nd.contrib_start[cell], k1 = P.nd.contrib_start[cell + 1];
         R sx = 0, sy = 0, kx = 0, ky = 0;
         // batches of U entries per lane: all index loads, then all value loads,
         // then the sums in list order
@@ -653,7 +655,7 @@ __device__ __forceinline__ void cols_type1_body(const DevPlan& P, int i1_base, c
         for (int base = k0 + lane; base < k1; base += L * U) {
             int idx[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) idx[u] = (base + u * L < k1) ? P.contrib[base + u * L] : -1;
+            for (int u = 0; u < U; ++u) idx[u] = (base + u * L < k1) ? P.nd.contrib[base + u * L] : -1;
             cpx<R> t[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) t[u] = (idx[u] >= 0) ? tiles[idx[u]] : cpx<R>{R(0), R(0)};
@@ -688,7 +690,7 @@ __device__ __forceinline__ void cols_type1_body(const DevPlan& P, int i1_base, c
     __syncthreads();
     const int c = g % COLS;
     const int i1 = i1_base + c;
-    const bool active = i1 < q;
+    const bool active = i1 < P.nd.col_hi;
     const cpx<R>* staged = lds_all + c * LP;
     cpx<R> v[16];
 #pragma unroll
@@ -740,7 +742,7 @@ __device__ __forceinline__ void rows_inverse_body(const DevPlan& P, R* __restric
     const cpx<R>* tw = static_cast<const cpx<R>*>(P.twr);
     const cpx<R>* xt = static_cast<const cpx<R>*>(P.xt);
     const cpx<R>* u = static_cast<const cpx<R>*>(P.u);
-    const int q = P.patch, lo = P.patch_lo;
+    const int q = P.patch, lo = P.patch_lo, c0 = P.nd.col_lo, c1 = P.nd.col_hi;
     // (F/2+1) G entries (column m, row gg), row index fastest; every load is
     // issued unconditionally (clamped index) so that all of them are in flight
     // at once
@@ -763,10 +765,12 @@ __device__ __forceinline__ void rows_inverse_body(const DevPlan& P, R* __restric
             const int ia = posmod_dev(m - lo, F);
             const int ib = posmod_dev(-m - lo, F);
             const cpx<R>* urow = u + static_cast<size_t>(r) * q;
-            const cpx<R> ua0 = urow[ia < q ? ia : q - 1];
-            const cpx<R> ub0 = urow[ib < q ? ib : q - 1];
-            const cpx<R> ua = (ia < q) ? ua0 : cpx<R>{R(0), R(0)};
-            const cpx<R> ub = (ib < q) ? ub0 : cpx<R>{R(0), R(0)};
+            // columns outside [c0, c1) hold no taps and are not written
+            const bool in_a = ia >= c0 && ia < c1, in_b = ib >= c0 && ib < c1;
+            const cpx<R> ua0 = urow[in_a ? ia : c0];
+            const cpx<R> ub0 = urow[in_b ? ib : c0];
+            const cpx<R> ua = in_a ? ua0 : cpx<R>{R(0), R(0)};
+            const cpx<R> ub = in_b ? ub0 : cpx<R>{R(0), R(0)};
             hh = {R(0.5) * (ua.x + ub.x), R(0.5) * (ua.y - ub.y)};
         }
         // position m: X + i H;  position F - m: conj X + i conj H (the clamped

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(FftShape<LOG>::NT * lines_per_block<LOG>()) void k_
 template <typename R, int LOG, int DIR>
 __global__ __launch_bounds__(FftShape<LOG>::NT) void k_cols_type2(DevPlan P) {
     __shared__ cpx<R> lds_all[lds_group_stride(1 << LOG)];
-    cols_type2_body<R, LOG, DIR, 1, false>(P, blockIdx.x, lds_all);
+    cols_type2_body<R, LOG, DIR, 1, false>(P, P.nd.col_lo + blockIdx.x, lds_all);
 }
 
 template <typename R, int MODE, int WMAX, int W>
@@ -87,7 +87,7 @@ template <typename R, int LOG, int DIR>
 __global__ __launch_bounds__(FftShape<LOG>::NT * lines_per_block<LOG>()) void k_cols_type1(DevPlan P) {
     constexpr int G = lines_per_block<LOG>();
     __shared__ cpx<R> lds_all[G * lds_group_stride(1 << LOG)];
-    cols_type1_body<R, LOG, DIR, G, 1, false>(P, blockIdx.x, lds_all);
+    cols_type1_body<R, LOG, DIR, G, 1, false>(P, P.nd.col_lo + blockIdx.x, lds_all);
 }
 
 template <typename R, int LOG, int DIR, bool USE_I1, bool USE_I2, bool EXACT, int G>
@@ -157,7 +157,7 @@ hipError_t launch_cols_highfreq(const DevPlan& P, int dir, hipStream_t s) {
 
 template <typename R, int LOG>
 hipError_t launch_cols_type2(const DevPlan& P, int dir, hipStream_t s) {
-    const int blocks = P.patch;
+    const int blocks = P.nd.col_hi - P.nd.col_lo;
     if (dir < 0) PHI_LAUNCH((k_cols_type2<R, LOG, -1>), dim3(blocks), dim3(FftShape<LOG>::NT), 0, s, P);
     else PHI_LAUNCH((k_cols_type2<R, LOG, 1>), dim3(blocks), dim3(FftShape<LOG>::NT), 0, s, P);
     return hipGetLastError();
@@ -166,7 +166,7 @@ hipError_t launch_cols_type2(const DevPlan& P, int dir, hipStream_t s) {
 template <typename R, int LOG>
 hipError_t launch_cols_type1(const DevPlan& P, int dir, hipStream_t s) {
     constexpr int G = lines_per_block<LOG>();
-    const int blocks = P.patch;   // one window column per block
+    const int blocks = P.nd.col_hi - P.nd.col_lo;   // one window column per block
     if (dir < 0) PHI_LAUNCH((k_cols_type1<R, LOG, -1>), dim3(blocks), dim3(FftShape<LOG>::NT * G), 0, s, P);
     else PHI_LAUNCH((k_cols_type1<R, LOG, 1>), dim3(blocks), dim3(FftShape<LOG>::NT * G), 0, s, P);
     return hipGetLastError();
@@ -253,7 +253,7 @@ hipError_t run_rows_inverse(const DevPlan& P, void* out, int dir, int use_i1, in
 
 template <typename R, int MODE>
 hipError_t run_nodes(const DevPlan& P, const void* coef, void* out, hipStream_t s) {
-    const dim3 grid(P.n_sub), block(kNodeThreadsSingle);
+    const dim3 grid(P.nd.n_sub), block(kNodeThreadsSingle);
     const cpx<R>* c = static_cast<const cpx<R>*>(coef);
     cpx<R>* o = static_cast<cpx<R>*>(out);
     // the node stage of a solve takes its kernel width as a template argument
@@ -295,9 +295,12 @@ hipError_t run_nodes(const DevPlan& P, const void* coef, void* out, hipStream_t 
     } while (0)
 
 template <typename R>
-hipError_t enqueue_typed(const DevPlan& P, const StreamSet& ss, Stage stage, const void* in, void* out, int adjoint,
+hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, const void* in, void* out, int adjoint,
                          hipStream_t s, KernelTimer* timer) {
-    PHI_TRY(check_twiddles(P));
+    PHI_TRY(check_twiddles(plan));
+    DevPlan P = plan;
+    // the type-2 and type-1 stages take or give a coefficient per node
+    if (stage == Stage::Type2 || stage == Stage::Type1) P.nd = P.nd_all;
     // forward solve: type-2 side and the first I1 transforms with e^{-...};
     // the transposed solve reverses every direction
     const int dir = adjoint ? 1 : -1;

@@ -8,6 +8,18 @@
 
 namespace phi {
 
+// One sorted node set on the device (NodeSet of the host plan).
+struct NodeTables {
+    const double* q;        // [M] I2 weights q_j (without h^2)
+    const int* cell;        // [2 M] first-tap window cell (x, y)
+    const void* taps;       // [M][2][w] kernel tap values, data precision
+    const int* sub;         // [4 n_sub] bin x, bin y, first node, node count
+    const int* contrib_start;  // [Q^2 + 1] tile entries summed into window cell x*Q + y
+    const int* contrib;        // flat tile indices
+    int n_sub;
+    int col_lo, col_hi;     // window columns the taps touch
+};
+
 // Everything a kernel needs, passed by value.  All pointers are device
 // pointers into the plan's single allocation.
 struct DevPlan {
@@ -28,14 +40,9 @@ struct DevPlan {
     const double* gx;       // [2 (F/2+1)] I1 multiplier factors along x
     const double* gy;       // [2 F] I1 multiplier factors along y
     const void* gyr;        // [F] (b, 1 - e^{-b}) pairs of gy in the data precision
-    const double* q;        // [M] I2 weights q_j (without h^2)
-    // node tables
-    const int* cell;        // [2 M] first-tap window cell (x, y)
-    const void* taps;       // [M][2][w] kernel tap values, data precision
-    const int* sub;         // [4 n_sub] bin x, bin y, first node, node count
-    const int* contrib_start;  // [Q^2 + 1] tile entries summed into window cell x*Q + y
-    const int* contrib;        // flat tile indices
-    int n_sub, bin, tile;      // subproblems, bin side, tile side E = bin + w - 1
+    NodeTables nd;          // the nodes this launch runs on: a solve's half plane, or all (enqueue's stages)
+    NodeTables nd_all;      // every node, for the type-2 and type-1 stages
+    int bin, tile;          // bin side, tile side E = bin + w - 1
     const void* twr;        // register-FFT stage twiddles, data precision, twr_count complex
     int twr_count;
     const void* twn;        // the same for length N (periodic solver), twn_count complex
