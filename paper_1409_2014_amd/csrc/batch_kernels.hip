@@ -41,7 +41,7 @@ static_assert(FftShape<kBatchMaxLogFine>::NT * batch_lines(kBatchMaxLogFine) == 
               "batched blocks hold whole transforms");
 static_assert(FftShape<kBatchMinLogFine>::NT * batch_lines(kBatchMinLogFine) == kBatchThreads,
               "batched blocks hold whole transforms");
-static_assert(kNodeThreads == kBatchThreads, "node blocks have the batched block size");
+static_assert(kNodeWaves * 64 == kBatchThreads && kNodeThreads == kBatchThreads, "node blocks have the batched block size");
 
 // Calls BODY with a compile-time length LOG_ for the member's fine-grid side.
 #define PHI_BATCH_LOG(LOGV, BODY)                                        \
@@ -88,10 +88,18 @@ __global__ __launch_bounds__(kBatchThreads) void kb_cols(BatchDev B, const WorkI
     }
 }
 
+template <typename R>
+__global__ __launch_bounds__(kBatchThreads) void kb_nodes_group(BatchDev B) {
+    __shared__ NodeGroupLds s;
+    const WorkItem w = B.nodes[blockIdx.x];
+    const DevPlan P = B.members[w.member];
+    nodes_group_body<R>(P, w.item, s);
+}
+
 template <typename R, int WMAX>
 __global__ __launch_bounds__(kBatchThreads) void kb_nodes(BatchDev B) {
     __shared__ NodeLds<R, WMAX> s;
-    const WorkItem w = B.nodes[blockIdx.x];
+    const WorkItem w = B.nodes_gen[blockIdx.x];
     const DevPlan P = B.members[w.member];
     nodes_body<R, 0, kNodeThreads, WMAX>(P, w.item, nullptr, nullptr, s);
 }
@@ -150,12 +158,13 @@ hipError_t enqueue_batch_dir(const BatchDev& B, const StreamSet& ss, const void*
         PHI_TRY_B(hipEventRecord(ss.fork, s));
         PHI_TRY_B(hipStreamWaitEvent(side, ss.fork, 0));
     }
+    PHI_LAUNCH_B("nodes", B.n_nodes, side, PHI_LAUNCH((kb_nodes_group<R>), dim3(B.n_nodes), blk, 0, side, B));
     if (B.wide_kernel)
-        PHI_LAUNCH_B("nodes", B.n_nodes, side,
-                     PHI_LAUNCH((kb_nodes<R, kMaxKernelWidth>), dim3(B.n_nodes), blk, 0, side, B));
+        PHI_LAUNCH_B("nodes", B.n_nodes_gen, side,
+                     PHI_LAUNCH((kb_nodes<R, kMaxKernelWidth>), dim3(B.n_nodes_gen), blk, 0, side, B));
     else
-        PHI_LAUNCH_B("nodes", B.n_nodes, side,
-                     PHI_LAUNCH((kb_nodes<R, kMaxEsWidth>), dim3(B.n_nodes), blk, 0, side, B));
+        PHI_LAUNCH_B("nodes", B.n_nodes_gen, side,
+                     PHI_LAUNCH((kb_nodes<R, kMaxEsWidth>), dim3(B.n_nodes_gen), blk, 0, side, B));
     PHI_LAUNCH_B("cols_type1", B.n_cols1, side,
                  PHI_LAUNCH((kb_cols_type1<R, -DIR>), dim3(B.n_cols1), blk, 0, side, B));
     if (ss.side) PHI_TRY_B(hipEventRecord(ss.join, side));

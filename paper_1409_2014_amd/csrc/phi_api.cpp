@@ -144,7 +144,8 @@ WorkParts layout_work(const phi::HostPlan& hp, size_t es, Layout& L) {
     w.tt = L.take(q * cs * 2 * es);
     w.win = L.take(q * q * 2 * es);
     w.pts = L.take(m * 2 * es);
-    w.tiles = L.take(static_cast<size_t>(hp.n_sub) * hp.tile * hp.tile * 2 * es);
+    w.tiles = L.take(std::max(static_cast<size_t>(hp.n_sub) * hp.tile_cells,
+                              static_cast<size_t>(hp.half.n_sub) * hp.half.tile_cells) * 2 * es);
     w.u = L.take(n * q * 2 * es);
     return w;
 }
@@ -261,6 +262,7 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
         nt.contrib_start = reinterpret_cast<const int*>(base + np.cst.off);
         nt.contrib = reinterpret_cast<const int*>(base + np.con.off);
         nt.n_sub = ns.n_sub;
+        nt.grouped = ns.grouped ? 1 : 0;
         nt.col_lo = ns.col_lo;
         nt.col_hi = ns.col_hi;
         return nt;
@@ -617,14 +619,14 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
             return plan->sets[plan->member_set[a]].n > plan->sets[plan->member_set[b]].n;
         });
-        std::vector<phi::WorkItem> rows, cols, cols_t2, cols_mixed, nodes, cols1;
+        std::vector<phi::WorkItem> rows, cols, cols_t2, cols_mixed, nodes, nodes_gen, cols1;
         for (int i : order) {
             const phi::HostPlan& hp = plan->sets[plan->member_set[i]];
             const int g = phi::batch_lines(hp.log_fine);
             push_items(&rows, i, 0, 0, hp.n, g);
             push_items(hp.component == 2 ? &cols_mixed : &cols, i, 0, 0, hp.n_fine / 2 + 1, g);
             push_items(&cols_t2, i, 1, hp.half.col_lo, hp.half.col_hi, g);
-            push_items(&nodes, i, 0, 0, hp.half.n_sub, 1);
+            push_items(hp.half.grouped ? &nodes : &nodes_gen, i, 0, 0, hp.half.n_sub, 1);
             push_items(&cols1, i, 0, hp.half.col_lo, hp.half.col_hi, g);
         }
         // one allocation: table sets, member workspaces, device views, work tables
@@ -640,6 +642,7 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         const Part p_cols_t2 = L.take(sizeof(phi::WorkItem) * cols_t2.size());
         const Part p_cols_mixed = L.take(sizeof(phi::WorkItem) * cols_mixed.size());
         const Part p_nodes = L.take(sizeof(phi::WorkItem) * nodes.size());
+        const Part p_nodes_gen = L.take(sizeof(phi::WorkItem) * nodes_gen.size());
         const Part p_cols1 = L.take(sizeof(phi::WorkItem) * cols1.size());
         plan->block_bytes = L.cursor;
         e = hipMalloc(&plan->block, L.cursor);
@@ -669,6 +672,7 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         if (e == hipSuccess) e = up(p_cols_t2, cols_t2.data());
         if (e == hipSuccess) e = up(p_cols_mixed, cols_mixed.data());
         if (e == hipSuccess) e = up(p_nodes, nodes.data());
+        if (e == hipSuccess) e = up(p_nodes_gen, nodes_gen.data());
         if (e == hipSuccess) e = up(p_cols1, cols1.data());
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
@@ -685,6 +689,7 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         b.cols_t2 = reinterpret_cast<const phi::WorkItem*>(base + p_cols_t2.off);
         b.cols_mixed = reinterpret_cast<const phi::WorkItem*>(base + p_cols_mixed.off);
         b.nodes = reinterpret_cast<const phi::WorkItem*>(base + p_nodes.off);
+        b.nodes_gen = reinterpret_cast<const phi::WorkItem*>(base + p_nodes_gen.off);
         b.cols1 = reinterpret_cast<const phi::WorkItem*>(base + p_cols1.off);
         b.n_rows = static_cast<int>(rows.size());
         b.n_cols = static_cast<int>(cols.size());
@@ -692,6 +697,7 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         b.n_cols_mixed = static_cast<int>(cols_mixed.size());
         for (const phi::HostPlan& hp : plan->sets) b.wide_kernel |= (hp.width > phi::kMaxEsWidth) ? 1 : 0;
         b.n_nodes = static_cast<int>(nodes.size());
+        b.n_nodes_gen = static_cast<int>(nodes_gen.size());
         b.n_cols1 = static_cast<int>(cols1.size());
         plan->host = plan->sets[plan->member_set[0]];
         phi_status sst = create_streams(plan);

@@ -409,59 +409,67 @@ void polar_nodes(const HostPlan& hp, std::vector<double>* kx, std::vector<double
 
 namespace {
 
-// Sorts the nodes listed in `pick` (indices into kx, ky, q; weights times
-// `weight`) and builds their subproblems and tile-reduction lists.
-phi_status build_node_set(const HostPlan& hp, const std::vector<double>& kx, const std::vector<double>& ky,
-                          const std::vector<double>& q, const std::vector<int>& pick, double weight,
-                          NodeSet* set, std::string* err) {
-    const int nf = hp.n_fine, w = hp.width;
+// First kernel taps (window cells) and tap values of all polar nodes, in their
+// natural order.
+struct NodeTaps {
+    std::vector<int> cx, cy;
+    std::vector<double> val;     // [M][2][w] psi(u - l), l = l0 .. l0 + w - 1, x then y
+};
+
+phi_status node_taps(const HostPlan& hp, const std::vector<double>& kx, const std::vector<double>& ky, NodeTaps* nt,
+                     std::string* err) {
+    const int nf = hp.n_fine, w = hp.width, m = hp.n_nodes;
     const double half_w = 0.5 * w;
-    const int m = static_cast<int>(pick.size());
     const int q_side = hp.patch, lo = hp.patch_lo;
-    std::vector<double> ux(m), uy(m);
-    std::vector<int> cx(m), cy(m);
-    for (int i = 0; i < m; ++i) {
+    nt->cx.resize(m);
+    nt->cy.resize(m);
+    nt->val.resize(static_cast<size_t>(m) * 2 * w);
+    for (int j = 0; j < m; ++j) {
         // t_j / Delta with t_j = 2 pi h k_j, Delta = 2 pi / n_fine: node position in cells
-        ux[i] = nf * hp.h * kx[pick[i]];
-        uy[i] = nf * hp.h * ky[pick[i]];
+        const double ux = nf * hp.h * kx[j], uy = nf * hp.h * ky[j];
         // first tap l0 = ceil(u - w/2), as a window cell (wrapped when the window is
         // the whole periodic fine grid)
-        const int ax = posmod(static_cast<int>(std::ceil(ux[i] - half_w)) - lo, nf);
-        const int ay = posmod(static_cast<int>(std::ceil(uy[i] - half_w)) - lo, nf);
+        const double l0x = std::ceil(ux - half_w), l0y = std::ceil(uy - half_w);
+        const int ax = posmod(static_cast<int>(l0x) - lo, nf);
+        const int ay = posmod(static_cast<int>(l0y) - lo, nf);
         if (q_side < nf && (ax + w > q_side || ay + w > q_side)) {
             *err = "internal: node taps outside the fine-grid window";
             return PHI_ERR_INTERNAL;
         }
-        cx[i] = ax;
-        cy[i] = ay;
+        nt->cx[j] = ax;
+        nt->cy[j] = ay;
+        double* val = &nt->val[static_cast<size_t>(j) * 2 * w];
+        for (int t = 0; t < w; ++t) {
+            const double dx = ux - (l0x + t), dy = uy - (l0y + t);
+            val[t] = hp.gaussian_kernel ? std::exp(-hp.beta * dx * dx) : es_kernel(dx / half_w, hp.beta);
+            val[w + t] = hp.gaussian_kernel ? std::exp(-hp.beta * dy * dy) : es_kernel(dy / half_w, hp.beta);
+        }
+    }
+    return PHI_OK;
+}
+
+// Sorts the nodes listed in `pick` (indices into the natural order; weights
+// times `weight`) and builds their subproblems and tile-reduction lists.
+void build_node_set(const HostPlan& hp, const std::vector<double>& kx, const std::vector<double>& ky,
+                    const std::vector<double>& q, const NodeTaps& nt, const std::vector<int>& pick, double weight,
+                    bool grouped, NodeSet* set) {
+    const int w = hp.width;
+    const int m = static_cast<int>(pick.size());
+    const int q_side = hp.patch;
+    std::vector<int> cx(m), cy(m);
+    for (int i = 0; i < m; ++i) {
+        cx[i] = nt.cx[pick[i]];
+        cy[i] = nt.cy[pick[i]];
     }
     // bins of bin x bin window cells; nodes sorted by the bin of their first tap
     const int bin = hp.bin;
     const int nb = q_side / bin;        // the window side is a power of two >= 16
-    const bool whole = (q_side == nf);
+    const bool whole = (q_side == hp.n_fine);
     std::vector<int> key(m);
     for (int i = 0; i < m; ++i) key[i] = (cy[i] / bin) * nb + cx[i] / bin;
     std::vector<int> order(m);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key[a] < key[b]; });
-    set->kx.resize(m); set->ky.resize(m); set->q.resize(m);
-    set->cell.resize(2 * static_cast<size_t>(m));
-    set->taps.resize(static_cast<size_t>(m) * 2 * w);
-    for (int i = 0; i < m; ++i) {
-        const int o = order[i], j = pick[o];
-        set->kx[i] = kx[j]; set->ky[i] = ky[j]; set->q[i] = weight * q[j];
-        set->cell[2 * i] = cx[o];
-        set->cell[2 * i + 1] = cy[o];
-        // psi(u - l) for the w taps l = l0 .. l0 + w - 1
-        const double l0x = std::ceil(ux[o] - half_w), l0y = std::ceil(uy[o] - half_w);
-        for (int t = 0; t < w; ++t) {
-            const double dx = ux[o] - (l0x + t), dy = uy[o] - (l0y + t);
-            set->taps[(static_cast<size_t>(i) * 2 + 0) * w + t] =
-                hp.gaussian_kernel ? std::exp(-hp.beta * dx * dx) : es_kernel(dx / half_w, hp.beta);
-            set->taps[(static_cast<size_t>(i) * 2 + 1) * w + t] =
-                hp.gaussian_kernel ? std::exp(-hp.beta * dy * dy) : es_kernel(dy / half_w, hp.beta);
-        }
-    }
     // window columns the taps touch (all of them when the window wraps)
     set->col_lo = 0;
     set->col_hi = q_side;
@@ -470,8 +478,10 @@ phi_status build_node_set(const HostPlan& hp, const std::vector<double>& kx, con
         set->col_lo = *mm.first / bin * bin;
         set->col_hi = std::min(q_side, *mm.second + w);
     }
-    // subproblems: runs of at most sub_nodes nodes of one bin
+    // subproblems: runs of at most sub_nodes nodes of one bin, each in whole
+    // groups when grouped
     set->sub.clear();
+    std::vector<int> slot_node;          // index into pick per slot, -1 for padding
     int max_bin = 0;
     for (int i = 0; i < m;) {
         const int k = key[order[i]];
@@ -479,29 +489,60 @@ phi_status build_node_set(const HostPlan& hp, const std::vector<double>& kx, con
         while (e < m && key[order[e]] == k) ++e;
         max_bin = std::max(max_bin, e - i);
         for (int s0 = i; s0 < e; s0 += hp.sub_nodes) {
+            const int count = std::min(hp.sub_nodes, e - s0);
             set->sub.push_back(k % nb);
             set->sub.push_back(k / nb);
-            set->sub.push_back(s0);
-            set->sub.push_back(std::min(hp.sub_nodes, e - s0));
+            set->sub.push_back(static_cast<int>(slot_node.size()));
+            set->sub.push_back(count);
+            for (int c = 0; c < count; ++c) slot_node.push_back(order[s0 + c]);
+            while (grouped && slot_node.size() % kNodeGroup) slot_node.push_back(-1);
         }
         i = e;
     }
     set->n_sub = static_cast<int>(set->sub.size() / 4);
     set->max_cell_nodes = max_bin;
+    set->grouped = grouped;
+    const size_t slots = slot_node.size();
+    const int row = grouped ? kNodeGroup : w;      // entries of one axis of a node's taps
+    set->q.assign(slots, 0.0);
+    set->taps.assign(slots * 2 * row, 0.0);
+    if (!grouped) {
+        set->kx.resize(slots);
+        set->ky.resize(slots);
+        set->cell.resize(2 * slots);
+    }
+    for (size_t i = 0; i < slots; ++i) {
+        if (slot_node[i] < 0) continue;
+        const int o = slot_node[i], j = pick[o];
+        set->q[i] = weight * q[j];
+        const double* val = &nt.val[static_cast<size_t>(j) * 2 * w];
+        // a grouped node's taps start at its first tap's place in the tile
+        const int ox = grouped ? cx[o] % bin : 0, oy = grouped ? cy[o] % bin : 0;
+        std::copy(val, val + w, &set->taps[i * 2 * row + ox]);
+        std::copy(val + w, val + 2 * w, &set->taps[(i * 2 + 1) * row + oy]);
+        if (!grouped) {
+            set->kx[i] = kx[j];
+            set->ky[i] = ky[j];
+            set->cell[2 * i] = cx[o];
+            set->cell[2 * i + 1] = cy[o];
+        }
+    }
     // window cell <- tile entries: every tile cell inside the box its nodes' taps
     // can reach, mapped to its window cell (wrapped when the window is periodic);
     // the lists are in subproblem order (two passes: count, then place)
-    const int E = hp.tile;
+    const int E = grouped ? kNodeGroup : hp.tile;      // tile row length
+    set->tile_cells = E * E;
     auto each_entry = [&](auto&& visit) {
         for (int sidx = 0; sidx < set->n_sub; ++sidx) {
             const int bx = set->sub[4 * sidx], by = set->sub[4 * sidx + 1];
             const int first = set->sub[4 * sidx + 2], count = set->sub[4 * sidx + 3];
             int ox0 = bin, ox1 = -1, oy0 = bin, oy1 = -1;
             for (int i = first; i < first + count; ++i) {
-                ox0 = std::min(ox0, set->cell[2 * i] - bx * bin);
-                ox1 = std::max(ox1, set->cell[2 * i] - bx * bin);
-                oy0 = std::min(oy0, set->cell[2 * i + 1] - by * bin);
-                oy1 = std::max(oy1, set->cell[2 * i + 1] - by * bin);
+                const int o = slot_node[i];
+                ox0 = std::min(ox0, cx[o] - bx * bin);
+                ox1 = std::max(ox1, cx[o] - bx * bin);
+                oy0 = std::min(oy0, cy[o] - by * bin);
+                oy1 = std::max(oy1, cy[o] - by * bin);
             }
             for (int cb = oy0; cb <= oy1 + w - 1; ++cb) {
                 for (int ca = ox0; ca <= ox1 + w - 1; ++ca) {
@@ -528,7 +569,6 @@ phi_status build_node_set(const HostPlan& hp, const std::vector<double>& kx, con
     set->contrib.resize(set->contrib_start.back());
     std::vector<int32_t> next(set->contrib_start.begin(), set->contrib_start.end() - 1);
     each_entry([&](int cell, int entry) { set->contrib[next[cell]++] = entry; });
-    return PHI_OK;
 }
 
 }  // namespace
@@ -555,10 +595,12 @@ phi_status build_host_plan(const phi_params* p, HostPlan* hp, std::string* err) 
             half.push_back(kx[a] >= kx[b] ? a : b);
         }
     }
-    st = build_node_set(*hp, kx, ky, q, all, 1.0, hp, err);
+    NodeTaps taps;
+    st = node_taps(*hp, kx, ky, &taps, err);
     if (st != PHI_OK) return st;
-    st = build_node_set(*hp, kx, ky, q, half, 2.0, &hp->half, err);
-    if (st != PHI_OK) return st;
+    build_node_set(*hp, kx, ky, q, taps, all, 1.0, false, hp);
+    // the matrix-instruction kernel holds a tile of 16 x 16 window cells
+    build_node_set(*hp, kx, ky, q, taps, half, 2.0, hp->tile <= kNodeGroup, &hp->half);
 
     // ---- deconvolution factors 2 pi / (n_fine psi_hat(n')) ---------------------
     // psi(x) = phi(x / a) with a = (w/2) Delta the kernel half-width in radians:

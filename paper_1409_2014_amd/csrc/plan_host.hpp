@@ -23,6 +23,7 @@ constexpr int kMaxTile = 31;          // largest spread tile side bin + w - 1
 constexpr int kBinSize = 4;            // default bin side in fine-grid cells (measured best or equal)
 constexpr int kMaxBinSize = 16;        // largest bin side
 constexpr int kMaxNodesPerSub = 64;    // most nodes per interp / spread subproblem
+constexpr int kNodeGroup = 16;         // nodes per matrix-instruction group, and its padded tile side
 
 // One sorted set of polar nodes with everything the node stage reads: plan
 // order, kernel taps, subproblems and the tile-reduction lists.
@@ -32,6 +33,12 @@ struct NodeSet {
     std::vector<double> taps;           // [M][2][w] psi(u_j - l0_j - t), x then y
     std::vector<int32_t> sub;           // [4 n_sub] bin x, bin y, first node, node count (<= 64)
     int n_sub = 0;
+    // grouped: the set is laid out for the matrix-instruction node kernel.  Every
+    // subproblem is padded to whole groups of 16 nodes (weight 0, taps 0), taps is
+    // [slots][2][16] with each node's taps at their place in the tile's 16 columns
+    // (x) and rows (y), tiles are 16 x 16; kx, ky and cell are empty.
+    bool grouped = false;
+    int tile_cells = 0;                 // entries of one subproblem's tile
     // reduction of the subproblem tiles onto the window: for window cell c = x * patch + y,
     // entries contrib_start[c] .. contrib_start[c+1]-1 of contrib hold flat tile indices
     std::vector<int32_t> contrib_start, contrib;

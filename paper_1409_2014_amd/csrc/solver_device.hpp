@@ -610,6 +610,114 @@ __device__ __forceinline__ void nodes_body(const DevPlan& P, int sidx, const cpx
     }
 }
 
+// The node stage of a solve on matrix instructions (grouped node sets: tiles of
+// at most 16 x 16 window cells).  With a group's 16 nodes as one dimension, both
+// steps are products of 16 x 16 matrices, K = 16, in v_mfma_f64_16x16x4:
+//   interp:  D[cb][j] = sum_ca tile[cb][ca] X[ca][j],  c_j = sum_cb Y[j][cb] D[cb][j]
+//   spread:  T[cb][ca] += sum_j (Y[j][cb] a_j) X[j][ca],  a_j = q_j h^2 c_j
+// where X and Y are the nodes' taps, zero outside the kernel.  A wave takes one
+// group at a time: operands come straight from global memory in the lane layout of
+// the instruction (lane l: row or column l % 16, k = l / 16 + 4 kk; the result's
+// register i is row l / 16 + 4 i), so the only barrier is before the four waves'
+// tiles are summed.  Both precisions accumulate in FP64 (same rate as FP32 on this
+// path, and no compensation is needed); the tile is rounded to the data precision
+// when it is stored.
+// The general kernel above is bound by its LDS reads (four per node and tile
+// cell); this one by the latency of two dependent global loads, 16 matrix
+// instructions and the store: 8.9 -> 4.8 us in FP64 and 6.7 -> 4.7 us in FP32 on
+// 64 x 128 nodes (91 blocks).  A wave's second group would start its loads after
+// the first one's result (about 2 us each: 128 nodes per subproblem 7 us, 256
+// 10.6 us, against 1 us less in the tile sums), so 64 nodes fill a block.
+constexpr int kNodeWaves = 4;
+
+struct NodeGroupLds {
+    double part[kNodeWaves][2][kNodeGroup * kNodeGroup];   // each wave's tile, re and im
+};
+
+template <typename R>
+__device__ __forceinline__ void nodes_group_body(const DevPlan& P, int sidx, NodeGroupLds& s) {
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    constexpr int T = kNodeGroup;
+    static_assert(T == 16, "one 16 x 16 x 4 matrix instruction per step");
+    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int lo = lane & 15, hi = lane >> 4;
+    const int* sub = P.nd.sub + 4 * sidx;
+    const int bx = sub[0], by = sub[1], first = sub[2], count = sub[3];
+    const int groups = (count + T - 1) / T;
+    const int q = P.patch;
+    const bool whole = (q == P.n_fine);
+    const int x0 = bx * P.bin, y0 = by * P.bin;
+    d4 t_re = {0, 0, 0, 0}, t_im = {0, 0, 0, 0};
+    for (int g = wave; g < groups; g += kNodeWaves) {
+        const size_t base = static_cast<size_t>(first) + g * T;
+        const R* tp = static_cast<const R*>(P.nd.taps) + base * 2 * T;
+        R xi[4], yi[4], xs[4], ys[4];
+        cpx<R> tl[4];
+        const cpx<R>* win = static_cast<const cpx<R>*>(P.win);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int kk = hi + 4 * k;
+            xi[k] = tp[lo * 2 * T + kk];          // X[ca = kk][j = lo]
+            yi[k] = tp[lo * 2 * T + T + kk];      // Y[j = lo][cb = kk]
+            xs[k] = tp[kk * 2 * T + lo];          // X[j = kk][ca = lo]
+            ys[k] = tp[kk * 2 * T + T + lo];      // Y[j = kk][cb = lo]
+            // tile[cb = lo][ca = kk]: zero beyond the window columns in use (the
+            // others are not written) and its last row
+            int wx = x0 + kk, wy = y0 + lo;
+            bool inside = true;
+            if (whole) {
+                wx &= q - 1;
+                wy &= q - 1;
+            } else {
+                inside = wx < P.nd.col_hi && wy < q;
+            }
+            tl[k] = inside ? win[static_cast<size_t>(wy) * q + wx] : cpx<R>{R(0), R(0)};
+        }
+        const double qh = P.nd.q[base + lo] * P.h2;
+        d4 d_re = {0, 0, 0, 0}, d_im = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            d_re = __builtin_amdgcn_mfma_f64_16x16x4f64(tl[k].x, xi[k], d_re, 0, 0, 0);
+            d_im = __builtin_amdgcn_mfma_f64_16x16x4f64(tl[k].y, xi[k], d_im, 0, 0, 0);
+        }
+        double c_re = 0.0, c_im = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            c_re += static_cast<double>(yi[i]) * d_re[i];
+            c_im += static_cast<double>(yi[i]) * d_im[i];
+        }
+        c_re += __shfl_xor(c_re, 16);
+        c_im += __shfl_xor(c_im, 16);
+        c_re += __shfl_xor(c_re, 32);
+        c_im += __shfl_xor(c_im, 32);
+        const double a_re = c_re * qh, a_im = c_im * qh;   // node lo, in every quarter of the wave
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double ar = __shfl(a_re, hi + 4 * k), ai = __shfl(a_im, hi + 4 * k);
+            const double y = ys[k];
+            t_re = __builtin_amdgcn_mfma_f64_16x16x4f64(y * ar, xs[k], t_re, 0, 0, 0);
+            t_im = __builtin_amdgcn_mfma_f64_16x16x4f64(y * ai, xs[k], t_im, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        s.part[wave][0][lane + 64 * i] = t_re[i];     // cell (cb = hi + 4 i) * 16 + (ca = lo)
+        s.part[wave][1][lane + 64 * i] = t_im[i];
+    }
+    __syncthreads();
+    static_assert(kNodeWaves * 64 == T * T, "one thread per tile cell");
+    const int c = threadIdx.x;
+    double v_re = s.part[0][0][c], v_im = s.part[0][1][c];
+#pragma unroll
+    for (int wv = 1; wv < kNodeWaves; ++wv) {
+        v_re += s.part[wv][0][c];
+        v_im += s.part[wv][1][c];
+    }
+    static_cast<cpx<R>*>(P.tiles)[static_cast<size_t>(sidx) * T * T + c] = {static_cast<R>(v_re),
+                                                                           static_cast<R>(v_im)};
+}
+
 // ---------------------------------------------------------------------------
 // cols_type1: sum the spread tiles onto one window column, FFT along y (only
 // the Q window inputs are non-zero), keep the N centred rows, times d(n2)

@@ -83,6 +83,12 @@ __global__ __launch_bounds__(kNodeThreadsSingle) void k_nodes(DevPlan P, const c
     nodes_body<R, MODE, kNodeThreadsSingle, WMAX, W>(P, blockIdx.x, coef, out, s);
 }
 
+template <typename R>
+__global__ __launch_bounds__(kNodeWaves * 64) void k_nodes_group(DevPlan P) {
+    __shared__ NodeGroupLds s;
+    nodes_group_body<R>(P, blockIdx.x, s);
+}
+
 template <typename R, int LOG, int DIR>
 __global__ __launch_bounds__(FftShape<LOG>::NT * lines_per_block<LOG>()) void k_cols_type1(DevPlan P) {
     constexpr int G = lines_per_block<LOG>();
@@ -256,12 +262,17 @@ hipError_t run_nodes(const DevPlan& P, const void* coef, void* out, hipStream_t 
     const dim3 grid(P.nd.n_sub), block(kNodeThreadsSingle);
     const cpx<R>* c = static_cast<const cpx<R>*>(coef);
     cpx<R>* o = static_cast<cpx<R>*>(out);
-    // the node stage of a solve takes its kernel width as a template argument
-    // whenever the width fits the ES tap store (every ES kernel, narrow Gaussians)
+    // the node stage of a solve: on matrix instructions where the set is laid out
+    // for them, else with the kernel width as a template argument whenever it fits
+    // the ES tap store (every ES kernel, narrow Gaussians)
 #define PHI_NODES_W(WV) \
     case WV: PHI_LAUNCH((k_nodes<R, MODE, kMaxEsWidth, WV>), grid, block, 0, s, P, c, o); break;
     static_assert(kMaxEsWidth == 16, "one case per ES width");
     if constexpr (MODE == 0) {
+        if (P.nd.grouped) {
+            PHI_LAUNCH((k_nodes_group<R>), grid, dim3(kNodeWaves * 64), 0, s, P);
+            return hipGetLastError();
+        }
         if (P.width <= kMaxEsWidth) {
             switch (P.width) {
                 PHI_NODES_W(2) PHI_NODES_W(3) PHI_NODES_W(4) PHI_NODES_W(5) PHI_NODES_W(6) PHI_NODES_W(7)

@@ -12,11 +12,12 @@ namespace phi {
 struct NodeTables {
     const double* q;        // [M] I2 weights q_j (without h^2)
     const int* cell;        // [2 M] first-tap window cell (x, y)
-    const void* taps;       // [M][2][w] kernel tap values, data precision
+    const void* taps;       // [M][2][w] kernel tap values, data precision (grouped: [slots][2][16])
     const int* sub;         // [4 n_sub] bin x, bin y, first node, node count
     const int* contrib_start;  // [Q^2 + 1] tile entries summed into window cell x*Q + y
     const int* contrib;        // flat tile indices
     int n_sub;
+    int grouped;            // laid out for the matrix-instruction node kernel
     int col_lo, col_hi;     // window columns the taps touch
 };
 
@@ -153,10 +154,11 @@ struct BatchDev {
     const WorkItem* cols = nullptr;    // I1 spectrum columns
     const WorkItem* cols_t2 = nullptr; // type-2 window columns
     const WorkItem* cols_mixed = nullptr;  // I1 columns of the members with the mixed multiplier
-    const WorkItem* nodes = nullptr;   // subproblems
+    const WorkItem* nodes = nullptr;   // subproblems of grouped node sets
+    const WorkItem* nodes_gen = nullptr;   // subproblems of the others
     const WorkItem* cols1 = nullptr;   // type-1 window columns
-    int n_rows = 0, n_cols = 0, n_cols_t2 = 0, n_cols_mixed = 0, n_nodes = 0, n_cols1 = 0;
-    int wide_kernel = 0;               // some member's kernel is wider than kMaxEsWidth
+    int n_rows = 0, n_cols = 0, n_cols_t2 = 0, n_cols_mixed = 0, n_nodes = 0, n_nodes_gen = 0, n_cols1 = 0;
+    int wide_kernel = 0;               // some member of nodes_gen has a kernel wider than kMaxEsWidth
 };
 
 // The static device scratch of phi_solve_noalloc: its size in bytes, and its
