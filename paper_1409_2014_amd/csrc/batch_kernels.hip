@@ -54,14 +54,36 @@ static_assert(kNodeWaves * 64 == kBatchThreads && kNodeThreads == kBatchThreads,
         default: break;                                                  \
     }
 
+// The same for the lengths of paired rows, exact or general bounds.
+#define PHI_BATCH_PAIR_LOG(LOGV, EXACT_BODY, BODY)                                        \
+    switch (LOGV) {                                                                       \
+        case 11:                                                                          \
+            if constexpr (kPairMinLogF32 <= 11 && sizeof(R) == 4) {                        \
+                constexpr int LOG_ = 11;                                                  \
+                if (2 * P.n == P.n_fine) EXACT_BODY; else BODY;                            \
+            }                                                                             \
+            break;                                                                        \
+        case 12: {                                                                        \
+            constexpr int LOG_ = 12;                                                      \
+            if (2 * P.n == P.n_fine) EXACT_BODY; else BODY;                                \
+            break;                                                                        \
+        }                                                                                 \
+        default: break;                                                                   \
+    }
+static_assert(kPairMinLogF32 == 11 && kPairMinLogF64 == 12, "the lengths PHI_BATCH_PAIR_LOG covers");
+
 template <typename R, int DIR>
 __global__ __launch_bounds__(kBatchThreads) void kb_rows_forward(BatchDev B, const R* __restrict__ in) {
     __shared__ cpx<R> lds_all[kBatchLds];
     const WorkItem w = B.rows[xcd_logical_block(blockIdx.x, gridDim.x)];
     const DevPlan P = B.members[w.member];
     const R* rho = in + B.offsets[w.member];
-    // members whose side is F/2 take the exact-bounds body (a uniform branch)
-    if (2 * P.n == P.n_fine) {
+    // members whose side is F/2 take the exact-bounds body, those with a
+    // deconvolution series the paired one (uniform branches)
+    if (P.pair_taps > 0) {
+        PHI_BATCH_PAIR_LOG(P.log_fine, (rows_forward_pair_body<R, LOG_, DIR, batch_lines(LOG_), true>(P, rho, w.item, lds_all)),
+                           (rows_forward_pair_body<R, LOG_, DIR, batch_lines(LOG_), false>(P, rho, w.item, lds_all)));
+    } else if (2 * P.n == P.n_fine) {
         PHI_BATCH_LOG(P.log_fine, (rows_forward_body<R, LOG_, DIR, batch_lines(LOG_), true>(P, rho, w.item, lds_all)));
     } else {
         PHI_BATCH_LOG(P.log_fine, (rows_forward_body<R, LOG_, DIR, batch_lines(LOG_), false>(P, rho, w.item, lds_all)));
@@ -119,7 +141,12 @@ __global__ __launch_bounds__(kBatchThreads) void kb_rows_inverse(BatchDev B, R* 
     const WorkItem w = B.rows[xcd_logical_block(blockIdx.x, gridDim.x)];
     const DevPlan P = B.members[w.member];
     R* dst = out + B.offsets[w.member];
-    if (2 * P.n == P.n_fine) {
+    if (P.pair_taps > 0) {
+        PHI_BATCH_PAIR_LOG(
+            P.log_fine,
+            (rows_inverse_pair_body<R, LOG_, DIR, true, true, batch_lines(LOG_), true>(P, dst, w.item, lds_all)),
+            (rows_inverse_pair_body<R, LOG_, DIR, true, true, batch_lines(LOG_), false>(P, dst, w.item, lds_all)));
+    } else if (2 * P.n == P.n_fine) {
         PHI_BATCH_LOG(P.log_fine,
                       (rows_inverse_body<R, LOG_, DIR, true, true, batch_lines(LOG_), true>(P, dst, w.item, lds_all)));
     } else {

@@ -99,7 +99,7 @@ struct NodeParts {
     Part q, cell, sub, cst, con, taps;
 };
 struct TableParts {
-    Part deconv, gx, gy, gyr, twr, twn;
+    Part delta, deconv, gx, gy, gyr, twr, twn;
     NodeParts half, all;
 };
 // everything a solve writes
@@ -121,6 +121,7 @@ NodeParts layout_nodes(const phi::NodeSet& ns, size_t es, Layout& L) {
 TableParts layout_tables(const phi::HostPlan& hp, size_t es, Layout& L) {
     TableParts t;
     const size_t n = hp.n, f = hp.n_fine;
+    t.delta = L.take(hp.delta.size() * 8);
     t.deconv = L.take(n * 8);
     t.gx = L.take(2 * (f / 2 + 1) * 8);
     t.gy = L.take(2 * f * 8);
@@ -166,6 +167,7 @@ hipError_t upload_tables(const phi::HostPlan& hp, const TableParts& t, char* bas
         return keep.back().data();
     };
     hipError_t e = hipSuccess;
+    if (e == hipSuccess) e = up(t.delta, hp.delta.data());
     if (e == hipSuccess) e = up(t.deconv, hp.deconv.data());
     if (e == hipSuccess) e = up(t.gx, hp.gx.data());
     if (e == hipSuccess) e = up(t.gy, hp.gy.data());
@@ -249,6 +251,8 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
     d->col_stride = static_cast<int>(column_stride(hp));
     d->h2 = hp.h * hp.h;
     d->inv_f2 = 1.0 / (f * f);
+    d->pair_taps = hp.pair_taps;
+    d->delta = reinterpret_cast<const double*>(base + t.delta.off);
     d->deconv = reinterpret_cast<const double*>(base + t.deconv.off);
     d->gx = reinterpret_cast<const double*>(base + t.gx.off);
     d->gy = reinterpret_cast<const double*>(base + t.gy.off);
@@ -623,7 +627,8 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         for (int i : order) {
             const phi::HostPlan& hp = plan->sets[plan->member_set[i]];
             const int g = phi::batch_lines(hp.log_fine);
-            push_items(&rows, i, 0, 0, hp.n, g);
+            if (hp.pair_taps > 0) push_items(&rows, i, 0, 0, hp.n / 2, g);     // pairs of rows
+            else push_items(&rows, i, 0, 0, hp.n, g);
             push_items(hp.component == 2 ? &cols_mixed : &cols, i, 0, 0, hp.n_fine / 2 + 1, g);
             push_items(&cols_t2, i, 1, hp.half.col_lo, hp.half.col_hi, g);
             push_items(hp.half.grouped ? &nodes : &nodes_gen, i, 0, 0, hp.half.n_sub, 1);

@@ -573,6 +573,141 @@ void build_node_set(const HostPlan& hp, const std::vector<double>& kx, const std
 
 }  // namespace
 
+namespace {
+
+// Least squares min |A c - b| by Householder QR in extended precision; A is
+// rows x cols, row-major, and is overwritten.
+void least_squares(std::vector<long double>& a, std::vector<long double>& b, int rows, int cols,
+                   std::vector<long double>* c) {
+    for (int k = 0; k < cols; ++k) {
+        long double s = 0.0L;
+        for (int i = k; i < rows; ++i) s += a[i * cols + k] * a[i * cols + k];
+        s = std::sqrt(s);
+        if (a[k * cols + k] > 0.0L) s = -s;
+        // the reflector v = x - s e_k, in place of column k below the diagonal
+        std::vector<long double> v(rows - k);
+        for (int i = k; i < rows; ++i) v[i - k] = a[i * cols + k];
+        v[0] -= s;
+        long double vv = 0.0L;
+        for (long double x : v) vv += x * x;
+        if (vv == 0.0L) continue;
+        for (int j = k; j <= cols; ++j) {
+            long double dot = 0.0L;
+            for (int i = k; i < rows; ++i) dot += v[i - k] * (j < cols ? a[i * cols + j] : b[i]);
+            dot *= 2.0L / vv;
+            for (int i = k; i < rows; ++i) (j < cols ? a[i * cols + j] : b[i]) -= dot * v[i - k];
+        }
+    }
+    c->assign(cols, 0.0L);
+    for (int k = cols - 1; k >= 0; --k) {
+        long double s = b[k];
+        for (int j = k + 1; j < cols; ++j) s -= a[k * cols + j] * (*c)[j];
+        (*c)[k] = s / a[k * cols + k];
+    }
+}
+
+// The deconvolution factors as a cosine series (HostPlan::delta).  With t = 2 pi
+// n'/F the factor is d0 / g(t), g(t) the kernel's transform over its value at
+// 0; a series p(t) = sum_j c_j cos(j t) with p g = 1 on |t| <= pi N/F exists to
+// rounding with few terms because its values beyond the grid are free.  They
+// are held small by rows of weight 1e-16 there (a series that is large beyond the
+// grid would amplify the row transform's rounding).  Accepted when the rounded
+// series is within a 100th of tol, or rounding, of the factors.  Least squares on
+// 4 B points, in extended precision, as the cosines are nearly dependent on the
+// grid's part of the circle.
+void fit_deconv_series(HostPlan* hp, double tol) {
+    hp->pair_taps = 0;
+    hp->delta.clear();
+    const int nf = hp->n_fine;
+    if (hp->log_fine < (hp->dtype == PHI_F32 ? kPairMinLogF32 : kPairMinLogF64)) return;
+    if (hp->patch == nf || hp->patch > kMaxPairWindow) return;
+    const long double edge = kPi * static_cast<long double>(hp->n) / nf;
+    // kernel transform at t: ES by a Gauss rule on [0, 1] (even integrand), the
+    // Gaussian in closed form
+    constexpr int kRule = 192;
+    static thread_local std::vector<double> gx, gw;
+    std::vector<long double> amp(kRule);
+    if (!hp->gaussian_kernel) {
+        if (gx.empty()) {
+            gx.resize(kRule);
+            gw.resize(kRule);
+            gauss_legendre(kRule, gx.data(), gw.data());
+            for (double& x : gx) x = 0.5 * (x + 1.0);
+        }
+        for (int i = 0; i < kRule; ++i) amp[i] = static_cast<long double>(gw[i]) * es_kernel(gx[i], hp->beta);
+    }
+    // g on the uniform points t_s = s step, s = 0 .. count
+    auto transform = [&](int count, std::vector<long double>* g) {
+        g->assign(count + 1, 0.0L);
+        const long double step = edge / count;
+        for (int s = 0; hp->gaussian_kernel && s <= count; ++s)
+            (*g)[s] = std::exp(-(s * step) * (s * step) / (4.0L * hp->beta));
+        for (int i = 0; !hp->gaussian_kernel && i < kRule; ++i) {
+            // cos(s phi) by its recurrence
+            const long double phi = step * 0.5L * hp->width * gx[i], two_c = 2.0L * std::cos(phi);
+            long double c0 = 1.0L, c1 = 0.5L * two_c;
+            for (int s = 0; s <= count; ++s) {
+                (*g)[s] += amp[i] * c0;
+                const long double c2 = two_c * c1 - c0;
+                c0 = c1;
+                c1 = c2;
+            }
+        }
+        const long double g0 = (*g)[0];
+        for (long double& x : *g) x /= g0;
+    };
+    const double target = std::max(hp->dtype == PHI_F32 ? 1e-9 : 1.5e-15, 1e-2 * tol);
+    // (the fewest terms that ever pass: fits take most of a small plan's time)
+    const int first = hp->dtype == PHI_F32 ? 8 : 5 * hp->n > 2 * nf ? 24 : 16;
+    for (int taps = first; taps <= kMaxPairTaps; taps += 4) {
+        // frequencies the series reaches from the window must not meet their mirror image
+        if (hp->patch / 2 + taps >= nf / 2) return;
+        const int ns = 4 * taps, far = 2 * taps, cols = taps + 1, rows = ns + far + 1;
+        std::vector<long double> g, a(static_cast<size_t>(rows) * cols), b(rows, 0.0L), c;
+        transform(ns, &g);
+        for (int s = 0; s < rows; ++s) {
+            // points 0 .. ns on the grid, then `far` points beyond it up to pi
+            const long double t =
+                s <= ns ? edge * s / ns : edge + (static_cast<long double>(kPi) - edge) * (s - ns) / far;
+            const long double wt = s <= ns ? g[s] : 1e-16L * g[ns];
+            const long double two_c = 2.0L * std::cos(t);
+            long double c0 = 1.0L, c1 = 0.5L * two_c;
+            for (int j = 0; j < cols; ++j) {
+                a[static_cast<size_t>(s) * cols + j] = wt * c0;
+                const long double c2 = two_c * c1 - c0;
+                c0 = c1;
+                c1 = c2;
+            }
+            if (s <= ns) b[s] = 1.0L;
+        }
+        least_squares(a, b, rows, cols, &c);
+        // the rounded series on points between the fitted ones
+        const int check = 2 * ns + 1;
+        transform(check, &g);
+        double worst = 0.0, size = 0.0;
+        for (int j = 0; j < cols; ++j) size += std::fabs(static_cast<double>(c[j]));
+        for (int s = 0; s <= check; ++s) {
+            const long double two_c = 2.0L * std::cos(edge * s / check);
+            long double c0 = 1.0L, c1 = 0.5L * two_c, p = 0.0L;
+            for (int j = 0; j < cols; ++j) {
+                p += static_cast<double>(c[j]) * c0;
+                const long double c2 = two_c * c1 - c0;
+                c0 = c1;
+                c1 = c2;
+            }
+            worst = std::max(worst, static_cast<double>(std::fabs(p * g[s] - 1.0L)));
+        }
+        if (!(worst <= target) || !(size <= 128.0)) continue;
+        hp->pair_taps = taps;
+        hp->delta.resize(cols);
+        const double d0 = hp->deconv[hp->n / 2];       // n' = 0
+        for (int j = 0; j < cols; ++j) hp->delta[j] = static_cast<double>(c[j]) * d0 * (j ? 0.5 : 1.0);
+        return;
+    }
+}
+
+}  // namespace
+
 phi_status build_host_plan(const phi_params* p, HostPlan* hp, std::string* err) {
     phi_status st = derive(p, hp, err);
     if (st != PHI_OK) return st;
@@ -626,6 +761,8 @@ phi_status build_host_plan(const phi_params* p, HostPlan* hp, std::string* err) 
         }
         hp->deconv[i] = 2.0 * kPi / (nf * ph);
     }
+
+    fit_deconv_series(hp, p->tol);
 
     // ---- I1 multiplier tables --------------------------------------------------
     const double s2 = hp->sigma * hp->sigma;

@@ -23,6 +23,10 @@ constexpr int kMaxTile = 31;          // largest spread tile side bin + w - 1
 constexpr int kBinSize = 4;            // default bin side in fine-grid cells (measured best or equal)
 constexpr int kMaxBinSize = 16;        // largest bin side
 constexpr int kMaxNodesPerSub = 64;    // most nodes per interp / spread subproblem
+constexpr int kMaxPairTaps = 32;       // longest deconvolution series of the paired row kernels
+// padded sides (log2) from which they are used
+constexpr int kPairMinLogF32 = 11, kPairMinLogF64 = 12;
+constexpr int kMaxPairWindow = 64;     // and their widest window
 constexpr int kNodeGroup = 16;         // nodes per matrix-instruction group, and its padded tile side
 
 // One sorted set of polar nodes with everything the node stage reads: plan
@@ -82,6 +86,13 @@ struct HostPlan : NodeSet {
     NodeSet half;                       // the nodes of the half plane kx >= 0, q doubled
     // tables
     std::vector<double> deconv;         // [N] 2 pi / (n_fine psi_hat(n')), n' = i - N/2
+    // the factors as a short cosine series on the fine grid, d(n') = sum_{|j| <= B}
+    // delta[|j|] e^{2 pi i j n'/F} on the grid's n' (B = pair_taps): the paired row
+    // kernels apply them along x as a convolution of the row spectrum.  Empty
+    // (pair_taps = 0) where no such series of at most kMaxPairTaps terms is
+    // accurate enough or the window does not leave room for it.
+    int pair_taps = 0;
+    std::vector<double> delta;          // [B + 1]
     std::vector<double> gx;             // [2 (F/2+1)] (a, 1 - e^{-a}),  a = kx^2 / sigma^2, kx = m/(n_fine h)
     std::vector<double> gy;             // [2 n_fine] (b, 1 - e^{-b}), signed frequency
     std::vector<double> twr;            // (re, im) per-stage twiddles of the register FFT of length n_fine

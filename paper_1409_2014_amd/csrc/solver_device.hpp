@@ -136,6 +136,114 @@ __device__ __forceinline__ void rows_forward_body(const DevPlan& P, const R* __r
     }
 }
 
+// Two spectrum values of one column, the rows of a pair, stored and loaded as one.
+template <typename R>
+struct alignas(16) cpx_pair {
+    cpx<R> a, b;
+};
+
+// Rows of the grid two at a time, G pairs per block: z = rho_a + i rho_b, one
+// F-point FFT for both rows.  With the row spectra X_a = (Z[m] + conj Z[-m]) / 2
+// and X_b = (Z[m] - conj Z[-m]) / (2i):
+//   XT      X_a, X_b on m = 0..F/2 (I1 half spectrum), the pair side by side;
+//   TT      the type-2 row window, the transform of rho d: the factor d(n1) is a
+//           cosine series (DevPlan::delta), so along x it is the convolution
+//           sum_j delta_|j| X[l - j] on the window columns in use, summed in FP64
+//           by 4 lanes per value; then times d(n2) of the row.
+// Against the one-row form above: half the transforms, LDS traffic and twiddles,
+// and runs of 2 G rows in each spectrum column.  The long rows are bound by the
+// scattered spectrum stores and loads (2048^2, timed apart: FP32 17.3 us with
+// 32-byte runs, 16.1 with 64-byte ones, 10 to 12 without the stores; FP64 38.2,
+// 32.5, 16 to 18), so G is chosen for 64-byte runs (launch_pairs).  The rows'
+// values do not depend on G.
+template <typename R, int LOG, int DIR, int G, bool EXACT>
+__device__ __forceinline__ void rows_forward_pair_body(const DevPlan& P, const R* __restrict__ rho, int pair0,
+                                                       cpx<R>* lds_all) {
+    using Sh = FftShape<LOG>;
+    constexpr int F = Sh::F;
+    constexpr int HALF = F / 2;
+    constexpr int NT = Sh::NT;
+    constexpr int LP = lds_group_stride(F);
+    constexpr int BT = NT * G;
+    const int n = EXACT ? F / 2 : P.n;
+    const int pairs = n >> 1;
+    const int g = threadIdx.x / NT;
+    const int tid = threadIdx.x - g * NT;
+    cpx<R>* lds = lds_all + g * LP;
+    const cpx<R>* tw = static_cast<const cpx<R>*>(P.twr);
+    // pairs at or beyond N/2 (the last block) transform the last pair and store nothing
+    const int pair = min(pair0 + g, pairs - 1);
+    const int half = EXACT ? F / 4 : (n >> 1);
+    const R* src = rho + static_cast<size_t>(2 * pair) * n + half;
+    cpx<R> v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int p = tid + NT * i;
+        v[i] = {R(0), R(0)};
+        if (i < 4 || i >= 12) {
+            const int o = (i < 4) ? p : p - F;
+            const bool inside = (i < 4) ? (p < half) : (p >= F - half);
+            if (inside) v[i] = {src[o], src[n + o]};
+        }
+    }
+    fft_reg<R, LOG, DIR>(v, lds, tw, tid);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lds[lds_pad(tid + NT * i)] = v[i];
+    __syncthreads();
+    cpx<R>* xt = static_cast<cpx<R>*>(P.xt) + 2 * static_cast<size_t>(pair0);
+    constexpr int ITEMS = (HALF + 1) * G;
+    constexpr int PASSES = (ITEMS + BT - 1) / BT;
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        const int idx = threadIdx.x + k * BT;
+        const int idc = idx < ITEMS ? idx : ITEMS - 1;
+        const int gg = idc % G;
+        const int m = idc / G;
+        const cpx<R>* l = lds_all + gg * LP;
+        const cpx<R> z = l[lds_pad(m)];
+        const cpx<R> zc = l[lds_pad((F - m) & (F - 1))];
+        if (idx < ITEMS && (EXACT || pair0 + gg < pairs))
+            *reinterpret_cast<cpx_pair<R>*>(xt + static_cast<size_t>(m) * P.col_stride + 2 * gg) = {
+                {R(0.5) * (z.x + zc.x), R(0.5) * (z.y - zc.y)}, {R(0.5) * (z.y + zc.y), R(-0.5) * (z.x - zc.x)}};
+    }
+    cpx<R>* tt = static_cast<cpx<R>*>(P.tt) + 2 * static_cast<size_t>(pair0);
+    constexpr int L = 4;
+    const int part = threadIdx.x % L;
+    const int B = P.pair_taps;
+    const int items = (P.nd.col_hi - P.nd.col_lo) * G;
+    for (int e = threadIdx.x / L; e < items; e += BT / L) {
+        const int gg = e % G;
+        const int i = P.nd.col_lo + e / G;
+        const int lf = P.patch_lo + i;
+        const cpx<R>* l = lds_all + gg * LP;
+        double ax = 0, ay = 0, bx = 0, by = 0;
+#pragma unroll 4
+        for (int j = part - B; j <= B; j += L) {
+            const double d = P.delta[j < 0 ? -j : j];
+            const cpx<R> z = l[lds_pad((lf - j) & (F - 1))];
+            const cpx<R> zc = l[lds_pad((j - lf) & (F - 1))];
+            const double zx = z.x, zy = z.y, cx = zc.x, cy = zc.y;
+            ax += d * (zx + cx);
+            ay += d * (zy - cy);
+            bx += d * (zy + cy);
+            by += d * (cx - zx);
+        }
+#pragma unroll
+        for (int off = 1; off < L; off <<= 1) {
+            ax += __shfl_xor(ax, off, L);
+            ay += __shfl_xor(ay, off, L);
+            bx += __shfl_xor(bx, off, L);
+            by += __shfl_xor(by, off, L);
+        }
+        if (part == 0 && (EXACT || pair0 + gg < pairs)) {
+            const double da = 0.5 * P.deconv[2 * (pair0 + gg)], db = 0.5 * P.deconv[2 * (pair0 + gg) + 1];
+            *reinterpret_cast<cpx_pair<R>*>(tt + static_cast<size_t>(i) * P.col_stride + 2 * gg) = {
+                {static_cast<R>(ax * da), static_cast<R>(ay * da)}, {static_cast<R>(bx * db), static_cast<R>(by * db)}};
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // cols_highfreq: FFT along y, multiplier, inverse FFT along y (in place in XT)
 // ---------------------------------------------------------------------------
@@ -168,6 +276,19 @@ template <typename R>
 __device__ __forceinline__ constexpr R tiny_normal() {
     if constexpr (sizeof(R) == 4) return 1.17549435e-38f;
     else return 2.2250738585072014e-308;
+}
+
+// FP32: the rotations by e^{i pi/4} inside the butterflies scale by sqrt(2) times
+// the float nearest 1/sqrt(2), 1 - 1.7e-8 (no float does better), and a quarter of
+// a radix-16 or radix-8 stage's terms pass one: the four transforms of a solve
+// lose 1.7e-8 of the amplitude per such stage, which the multiplier gives back.
+// Measured as the mean scale of a solve against float64 sums, 64^2 to 3000^2:
+// -5e-8 to -9e-8 before, within 1e-8 of 0 with it; the whole error, 1.2e-7 to
+// 2e-7, becomes that of rounding alone.  (FP64 constants lose nothing that matters.)
+template <typename R, int LOG>
+__device__ __forceinline__ constexpr R norm_loss() {
+    constexpr int stages = FftShape<LOG>::S16 + (FftShape<LOG>::REM == 3 ? 1 : 0);
+    return sizeof(R) == 4 ? R(1.7e-8) * R(stages) : R(0);
 }
 
 // Column m1 of the half spectrum (contiguous in XT, N values at centred y
@@ -250,6 +371,14 @@ __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base
     const R fs = static_cast<R>(P.freq_scale);
     const R fx = (mc == HALF) ? R(0) : static_cast<R>(mc) * fs;
     const R inv_sigma = static_cast<R>(P.inv_sigma);
+    // FP32: frequency indices of this thread's points (mx2 is positive at the
+    // origin too, where the numerator is 0; the mixed one is 0 on the Nyquist
+    // column), and A, 1 - A = e^{-a} with the sign and the power of two 1 / F^2
+    const R fy = static_cast<R>(tid);
+    const R mxn = mc == HALF ? R(0) : static_cast<R>(mc);
+    const R mx2 = static_cast<R>(mc) * static_cast<R>(mc) + tiny_normal<R>();
+    const R part_a = static_cast<R>(-P.gx[2 * mc + 1] * P.inv_f2);
+    const R part_e = static_cast<R>((P.gx[2 * mc + 1] - 1.0) * P.inv_f2);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const R b = gb[i].x;
@@ -262,6 +391,20 @@ __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base
         } else if constexpr (KIND == kKindCoulombErfc) {
             const R s2 = a + b;
             gfac = erf_over_x<R>(sqrt(s2), s2) * (inv_sigma * scale);
+        } else if constexpr (sizeof(R) == 4) {
+            // the quotient of the integer frequency indices (exact products up to
+            // 2^24), corrected by its remainder: within an ulp; A + B - A B as
+            // A + B e^{-a}, rounded once
+            const R my = fy + static_cast<R>(NT * i - (i < 8 ? 0 : F));
+            const R den = fma(my, my, mx2);
+            R num;
+            if constexpr (KIND == kKindMixed) num = (i == 8 && tid == 0) ? R(0) : mxn * my;
+            else num = ycomp ? my * my : mx2;
+            const R r = __builtin_amdgcn_rcpf(den);
+            const R q0 = num * r;
+            const R q = fma(fma(-q0, den, num), r, q0);
+            const R w = fma(B, part_e, part_a);
+            gfac = fma(q, w, (q * norm_loss<R, LOG>()) * w);   // less than half an ulp: added before rounding
         } else {
             R num;
             if constexpr (KIND == kKindMixed) {
@@ -918,6 +1061,152 @@ __device__ __forceinline__ void rows_inverse_body(const DevPlan& P, R* __restric
                 if (inside)
                     dst[o] = static_cast<R>(static_cast<double>(v[i].x) +
                                             static_cast<double>(v[i].y) * dpre[i < 4 ? i : i - 8]);
+            }
+        }
+    }
+}
+
+// Two rows at a time (see rows_forward_pair_body): V = (S_a + E_a) + i (S_b + E_b)
+// with S the Hermitian extension of a row's I1 half spectrum and E = sum_j
+// delta_|j| H[m - j] the type-1 row's Hermitian part H with its deconvolution,
+// in FP64; one inverse FFT, Phi_a = Re, Phi_b = Im.  E is zero beyond the window
+// by more than B.  The windows' H sits in the start of the transform buffers
+// while E is summed (into registers, the spectrum loads in flight), then the
+// spectrum takes their place and E is added.
+template <typename R, int LOG, int DIR, bool USE_I1, bool USE_I2, int G, bool EXACT>
+__device__ __forceinline__ void rows_inverse_pair_body(const DevPlan& P, R* __restrict__ out, int pair0,
+                                                       cpx<R>* lds_all) {
+    using Sh = FftShape<LOG>;
+    constexpr int F = Sh::F;
+    constexpr int HALF = F / 2;
+    constexpr int NT = Sh::NT;
+    constexpr int LP = lds_group_stride(F);
+    constexpr int BT = NT * G;
+    const int n = EXACT ? F / 2 : P.n;
+    const int pairs = n >> 1;
+    const int g = threadIdx.x / NT;
+    const int tid = threadIdx.x - g * NT;
+    cpx<R>* lds = lds_all + g * LP;
+    const cpx<R>* tw = static_cast<const cpx<R>*>(P.twr);
+    const cpx<R>* xt = static_cast<const cpx<R>*>(P.xt);
+    constexpr int ITEMS = (HALF + 1) * G;
+    constexpr int PASSES = (ITEMS + BT - 1) / BT;
+    cpx_pair<R> xr[PASSES];
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        const int idx = threadIdx.x + k * BT;
+        const int idc = idx < ITEMS ? idx : ITEMS - 1;
+        const int pair = min(pair0 + idc % G, pairs - 1);   // pairs past N/2 read the last one, never stored
+        xr[k] = cpx_pair<R>{{R(0), R(0)}, {R(0), R(0)}};
+        if constexpr (USE_I1)
+            xr[k] = *reinterpret_cast<const cpx_pair<R>*>(xt + static_cast<size_t>(idc / G) * P.col_stride + 2 * pair);
+    }
+    // E on m = 0 .. M-1: the NT threads of a transform do their pair's, PT lanes per value
+    constexpr int PT = NT >= 256 ? 4 : NT >= 128 ? 2 : 1;
+    constexpr int STEP = NT / PT;
+    constexpr int KMAX = (kMaxPairWindow / 2 + kMaxPairTaps + 1 + STEP - 1) / STEP;
+    const int B = P.pair_taps;
+    const int q = P.patch, lo = P.patch_lo, c0 = P.nd.col_lo, c1 = P.nd.col_hi;
+    const int lm = max(-(lo + c0), lo + c1 - 1);                      // |l| <= lm in the window columns
+    const int M = lm + B + 1;
+    const int part = tid % PT;
+    double ea[KMAX][2], eb[KMAX][2];
+    if constexpr (USE_I2) {
+        // H[l], l = 0 .. lm, of both rows (H[-l] = conj H[l])
+        const cpx<R>* u = static_cast<const cpx<R>*>(P.u);
+        const int items = (lm + 1) * 2 * G;
+        for (int e = threadIdx.x; e < items; e += BT) {
+            const int l = e % (lm + 1);
+            const int row = e / (lm + 1);                             // 2 gg + (0: a, 1: b)
+            const int gg = row >> 1;
+            const int r = 2 * min(pair0 + gg, pairs - 1) + (row & 1);
+            const int ia = l - lo, ib = -l - lo;
+            const bool in_a = ia >= c0 && ia < c1, in_b = ib >= c0 && ib < c1;
+            const cpx<R>* urow = u + static_cast<size_t>(r) * q;
+            const cpx<R> ua0 = urow[in_a ? ia : c0];
+            const cpx<R> ub0 = urow[in_b ? ib : c0];
+            const cpx<R> ua = in_a ? ua0 : cpx<R>{R(0), R(0)};
+            const cpx<R> ub = in_b ? ub0 : cpx<R>{R(0), R(0)};
+            lds_all[gg * LP + (row & 1) * (lm + 1) + l] = {R(0.5) * (ua.x + ub.x), R(0.5) * (ua.y - ub.y)};
+        }
+        __syncthreads();
+        const cpx<R>* ha = lds;
+        const cpx<R>* hb = ha + lm + 1;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const int m = tid / PT + k * STEP;
+            ea[k][0] = ea[k][1] = eb[k][0] = eb[k][1] = 0.0;
+            if (m < M) {
+                const int l1 = min(lm, m + B);
+#pragma unroll 4
+                for (int l = max(-lm, m - B) + part; l <= l1; l += PT) {
+                    const int al = l < 0 ? -l : l;
+                    const int j = m > l ? m - l : l - m;
+                    const double d = P.delta[j];
+                    const double ds = l < 0 ? -d : d;
+                    const cpx<R> a = ha[al], b = hb[al];
+                    ea[k][0] += d * a.x;
+                    ea[k][1] += ds * a.y;
+                    eb[k][0] += d * b.x;
+                    eb[k][1] += ds * b.y;
+                }
+            }
+#pragma unroll
+            for (int off = 1; off < PT; off <<= 1) {
+                ea[k][0] += __shfl_xor(ea[k][0], off, PT);
+                ea[k][1] += __shfl_xor(ea[k][1], off, PT);
+                eb[k][0] += __shfl_xor(eb[k][0], off, PT);
+                eb[k][1] += __shfl_xor(eb[k][1], off, PT);
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < PASSES; ++k) {
+        const int idx = threadIdx.x + k * BT;
+        const int gg = idx % G;
+        const int m = idx / G;
+        cpx<R>* l = lds_all + gg * LP;
+        const cpx<R> a = xr[k].a, b = xr[k].b;
+        // position m: S_a + i S_b;  position F - m: conj S_a + i conj S_b
+        if (idx < ITEMS) {
+            l[lds_pad(m)] = {a.x - b.y, a.y + b.x};
+            if (m > 0 && m < HALF) l[lds_pad(F - m)] = {a.x + b.y, b.x - a.y};
+        }
+    }
+    __syncthreads();
+    if constexpr (USE_I2) {
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const int m = tid / PT + k * STEP;
+            if (part == 0 && m < M) {
+                cpx<R>* p = lds + lds_pad(m);
+                *p = {static_cast<R>(p->x + (ea[k][0] - eb[k][1])), static_cast<R>(p->y + (ea[k][1] + eb[k][0]))};
+                if (m > 0) {
+                    cpx<R>* c = lds + lds_pad(F - m);
+                    *c = {static_cast<R>(c->x + (ea[k][0] + eb[k][1])), static_cast<R>(c->y + (eb[k][0] - ea[k][1]))};
+                }
+            }
+        }
+        __syncthreads();
+    }
+    cpx<R> v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = lds[lds_pad(tid + NT * i)];
+    fft_reg<R, LOG, DIR>(v, lds, tw, tid);
+    const int half = EXACT ? F / 4 : (n >> 1);
+    if ((EXACT || pair0 + g < pairs)) {
+        R* dst = out + static_cast<size_t>(2 * (pair0 + g)) * n + half;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int p = tid + NT * i;
+            if (i < 4 || i >= 12) {
+                const int o = (i < 4) ? p : p - F;
+                const bool inside = (i < 4) ? (p < half) : (p >= F - half);
+                if (inside) {
+                    dst[o] = v[i].x;
+                    dst[n + o] = v[i].y;
+                }
             }
         }
     }

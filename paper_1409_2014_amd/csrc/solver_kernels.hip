@@ -37,6 +37,8 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "solver_device.hpp"
 
 namespace phi {
@@ -54,6 +56,19 @@ constexpr int rows_per_wave() {
     return g < rows_per_block<R, LOG>() ? g : rows_per_block<R, LOG>();
 }
 constexpr int kRowsWideMinBlocks = 256;   // one wide block per CU at least, else the narrow width
+
+template <typename R, int LOG, int DIR, bool EXACT, int G>
+__global__ __launch_bounds__((FftShape<LOG>::NT * G)) void k_rows_forward_pair(DevPlan P, const R* __restrict__ rho) {
+    __shared__ cpx<R> lds_all[G * lds_group_stride(1 << LOG)];
+    rows_forward_pair_body<R, LOG, DIR, G, EXACT>(P, rho, xcd_logical_block(blockIdx.x, gridDim.x) * G, lds_all);
+}
+
+template <typename R, int LOG, int DIR, bool USE_I1, bool USE_I2, bool EXACT, int G>
+__global__ __launch_bounds__((FftShape<LOG>::NT * G)) void k_rows_inverse_pair(DevPlan P, R* __restrict__ out) {
+    __shared__ cpx<R> lds_all[G * lds_group_stride(1 << LOG)];
+    rows_inverse_pair_body<R, LOG, DIR, USE_I1, USE_I2, G, EXACT>(
+        P, out, xcd_logical_block(blockIdx.x, gridDim.x) * G, lds_all);
+}
 
 template <typename R, int LOG, int DIR, bool EXACT, int G>
 __global__ __launch_bounds__((FftShape<LOG>::NT * G)) void k_rows_forward(DevPlan P, const R* __restrict__ rho) {
@@ -108,6 +123,49 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * G)) void k_rows_inverse(DevPla
 // ---------------------------------------------------------------------------
 namespace {
 
+// Pairs per block of the paired row kernels: 64-byte runs of each spectrum
+// column (4 pairs in FP32, 2 in FP64) while the block fits 1024 threads and 140
+// KB of LDS, halved until every CU has a block.
+template <typename R, int LOG>
+constexpr int max_pairs() {
+    int g = sizeof(R) == 4 ? 4 : 2;
+    while (g > 1 && (FftShape<LOG>::NT * g > 1024 ||
+                     g * lds_group_stride(1 << LOG) * sizeof(cpx<R>) > static_cast<size_t>(140) * 1024))
+        g /= 2;
+    return g;
+}
+template <int GMAX, typename F>
+hipError_t launch_pairs(int pairs, F&& launch) {
+    if constexpr (GMAX > 1) {
+        if (pairs < kRowsWideMinBlocks * GMAX) return launch_pairs<GMAX / 2>(pairs, launch);
+    }
+    return launch(std::integral_constant<int, GMAX>());
+}
+
+template <typename R, int LOG, int DIR, int G>
+hipError_t launch_rows_forward_pair(const DevPlan& P, const R* src, hipStream_t s) {
+    constexpr int block = FftShape<LOG>::NT * G;
+    const int grid = (P.n / 2 + G - 1) / G;
+    if (2 * P.n == P.n_fine)
+        PHI_LAUNCH((k_rows_forward_pair<R, LOG, DIR, true, G>), dim3(grid), dim3(block), 0, s, P, src);
+    else
+        PHI_LAUNCH((k_rows_forward_pair<R, LOG, DIR, false, G>), dim3(grid), dim3(block), 0, s, P, src);
+    return hipGetLastError();
+}
+
+template <typename R, int LOG, int DIR, bool I1, bool I2, int G>
+hipError_t launch_rows_inverse_pair(const DevPlan& P, R* dst, hipStream_t s) {
+    constexpr int block = FftShape<LOG>::NT * G;
+    const int grid = (P.n / 2 + G - 1) / G;
+    if (I1 && I2 && 2 * P.n == P.n_fine)
+        PHI_LAUNCH((k_rows_inverse_pair<R, LOG, DIR, I1, I2, I1 && I2, G>), dim3(grid), dim3(block), 0, s, P,
+                   dst);
+    else
+        PHI_LAUNCH((k_rows_inverse_pair<R, LOG, DIR, I1, I2, false, G>), dim3(grid), dim3(block), 0, s, P,
+                   dst);
+    return hipGetLastError();
+}
+
 template <typename R, int LOG, int DIR, int G>
 hipError_t launch_rows_forward_g(const DevPlan& P, const R* src, hipStream_t s) {
     constexpr int block = FftShape<LOG>::NT * G;
@@ -119,6 +177,11 @@ hipError_t launch_rows_forward_g(const DevPlan& P, const R* src, hipStream_t s) 
 
 template <typename R, int LOG, int DIR>
 hipError_t launch_rows_forward_dir(const DevPlan& P, const R* src, hipStream_t s) {
+    if constexpr (LOG >= (sizeof(R) == 4 ? kPairMinLogF32 : kPairMinLogF64)) {
+        if (P.pair_taps > 0)
+            return launch_pairs<max_pairs<R, LOG>()>(
+                P.n / 2, [&](auto g) { return launch_rows_forward_pair<R, LOG, DIR, decltype(g)::value>(P, src, s); });
+    }
     constexpr int GW = rows_per_block<R, LOG>();
     if ((P.n + GW - 1) / GW < kRowsWideMinBlocks)
         return launch_rows_forward_g<R, LOG, DIR, rows_per_wave<R, LOG>()>(P, src, s);
@@ -192,6 +255,12 @@ hipError_t launch_rows_inverse_g(const DevPlan& P, R* dst, hipStream_t s) {
 
 template <typename R, int LOG, int DIR, bool I1, bool I2>
 hipError_t launch_rows_inverse_parts(const DevPlan& P, R* dst, hipStream_t s) {
+    if constexpr (LOG >= (sizeof(R) == 4 ? kPairMinLogF32 : kPairMinLogF64)) {
+        if (P.pair_taps > 0)
+            return launch_pairs<max_pairs<R, LOG>()>(P.n / 2, [&](auto g) {
+                return launch_rows_inverse_pair<R, LOG, DIR, I1, I2, decltype(g)::value>(P, dst, s);
+            });
+    }
     constexpr int GW = rows_per_block<R, LOG>();
     if ((P.n + GW - 1) / GW < kRowsWideMinBlocks)
         return launch_rows_inverse_g<R, LOG, DIR, I1, I2, rows_per_wave<R, LOG>()>(P, dst, s);

@@ -36,7 +36,9 @@ struct DevPlan {
     double freq_scale;      // 1 / (n_fine h sigma): k/sigma per fine-grid frequency index
     int col_stride;         // elements between consecutive columns of xt and tt (N + pad)
     double h2, inv_f2;
+    int pair_taps;          // B > 0: rows run in pairs (rows_*_pair_body), delta has B + 1 entries
     // FP64 tables
+    const double* delta;    // [B + 1] cosine series of deconv
     const double* deconv;   // [N] 2 pi / (n_fine psi_hat(n'))
     const double* gx;       // [2 (F/2+1)] I1 multiplier factors along x
     const double* gy;       // [2 F] I1 multiplier factors along y
