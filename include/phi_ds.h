@@ -75,6 +75,15 @@ phi_status phi_ds_plan(phi_ds_t ds, phi_plan_t* plan);
  * nonlinear substep. */
 phi_status phi_ds_forward(phi_ds_t ds, void* u, int32_t steps, void* v_store, void* phi_store, void* stream);
 
+/* phi_ds_forward for a run whose loss is read in FP64 (phi_ds_moments): an FP32
+ * stepper takes every potential solve in its plain arithmetic (all nodes, one row
+ * per transform) and the rotations from the library's sine and cosine, so that
+ * the trajectory, and with it the loss to all its digits, does not depend on which
+ * of the faster kernels a build or a size selects.  The same steps as
+ * phi_ds_forward within FP32 rounding, at the plain solve's speed; in FP64 the two
+ * are the same. */
+phi_status phi_ds_forward_plain(phi_ds_t ds, void* u, int32_t steps, void* v_store, void* phi_store, void* stream);
+
 /* Reverse pass of `steps` steps: g holds the gradient with respect to the
  * state after the steps and is overwritten with the gradient with respect to
  * the state before them.  v_store and phi_store are the stores a phi_ds_forward

@@ -111,6 +111,7 @@ def _declare(lib):
         "phi_ds_destroy": (st, [_P]),
         "phi_ds_plan": (st, [_P, ctypes.POINTER(_P)]),
         "phi_ds_forward": (st, [_P, _P, ctypes.c_int32, _P, _P, _P]),
+        "phi_ds_forward_plain": (st, [_P, _P, ctypes.c_int32, _P, _P, _P]),
         "phi_ds_backward": (st, [_P, _P, ctypes.c_int32, _P, _P, _P]),
         "phi_ds_moments": (st, [_P, _P, _P, _P]),
         "phi_ds_loss_grad": (st, [_P, _P, _P, _P]),
@@ -152,6 +153,7 @@ def exported_symbols():
         "phi_destroy", "phi_solve_timed", "phi_plan_get_info", "phi_plan_nodes", "phi_host_gauss_legendre", "phi_host_gauss_jacobi01",
         "phi_host_es_kernel", "phi_host_es_transform", "phi_host_polar_nodes",
         "phi_status_string", "phi_last_error",
-        "phi_ds_create", "phi_ds_substeps", "phi_ds_destroy", "phi_ds_plan", "phi_ds_forward", "phi_ds_backward",
+        "phi_ds_create", "phi_ds_substeps", "phi_ds_destroy", "phi_ds_plan", "phi_ds_forward",
+        "phi_ds_forward_plain", "phi_ds_backward",
         "phi_ds_moments", "phi_ds_loss_grad",
     ]

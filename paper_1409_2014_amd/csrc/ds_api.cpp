@@ -111,8 +111,9 @@ int table_of(std::vector<double>* times, double d) {
     return static_cast<int>(times->size()) - 1;
 }
 
-phi_status solve_potential(phi_ds_s* ds, const void* in, void* out, bool transpose, void* stream) {
+phi_status solve_potential(phi_ds_s* ds, const void* in, void* out, bool transpose, bool plain, void* stream) {
     if (ds->potential == PHI_DS_PERIODIC) return phi_solve_periodic(ds->plan, in, out, stream);
+    if (plain) return phi::solve_plain(ds->plan, in, out, stream);
     return transpose ? phi_solve_adjoint(ds->plan, in, out, stream) : phi_solve(ds->plan, in, out, stream);
 }
 
@@ -130,6 +131,44 @@ int table_after(const phi_ds_s* ds, int k, int total) {
         hipError_t e_ = (expr);                           \
         if (e_ != hipSuccess) return hip_err(e_, where);  \
     } while (0)
+
+// plain: FP32 runs in the plain arithmetic (phi_ds_forward_plain)
+phi_status forward(phi_ds_t ds, void* u, int32_t steps, void* v_store, void* phi_store, bool plain, void* stream) {
+    phi_status st = check(ds);
+    if (st != PHI_OK) return st;
+    if (!u || steps < 0) return err(PHI_ERR_INVALID_ARG, "NULL field or negative step count");
+    if (steps == 0) return PHI_OK;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const phi::DsDev& D = ds->dev;
+    const size_t nn = static_cast<size_t>(ds->n) * ds->n;
+    const int K = static_cast<int>(ds->non.size());
+    const int total = steps * K;
+    const phi::DsRowIn turn = plain && D.dtype == PHI_F32 ? phi::DsRowIn::NonlinearLibrary : phi::DsRowIn::Nonlinear;
+    char* vs = static_cast<char*>(v_store);
+    char* ps = static_cast<char*>(phi_store);
+    // the first linear substep; then per nonlinear substep: complete the linear
+    // substep (v_k, rho_k), Phi_k, the nonlinear substep fused into the next
+    // linear substep (consecutive linear substeps of two steps merged)
+    const int t0 = ds->lin_first_table;
+    DS_TRY(phi::ds_rows_forward(D, phi::DsRowIn::Plain, 0, t0, u, nullptr, nullptr, nullptr, nullptr, 0.0, s),
+           "ds rows_forward");
+    DS_TRY(phi::ds_cols(D, 0, t0, s), "ds cols");
+    for (int k = 0; k < total; ++k) {
+        const double ntau = ds->non[k % K] * ds->tau;
+        void* v = vs ? static_cast<void*>(vs + static_cast<size_t>(k) * nn * 2 * ds->elem) : ds->work_c;
+        void* pot = ps ? static_cast<void*>(ps + static_cast<size_t>(k) * nn * ds->elem) : ds->work_r2;
+        DS_TRY(phi::ds_rows_inverse(D, phi::DsRowOut::Density, v, ds->work_r1, nullptr, nullptr, ntau, s),
+               "ds rows_inverse");
+        st = solve_potential(ds, ds->work_r1, pot, false, plain, stream);
+        if (st != PHI_OK) return st;
+        const int tn = table_after(ds, k, total);
+        DS_TRY(phi::ds_rows_forward(D, turn, 0, tn, v, nullptr, pot, nullptr, nullptr, ntau, s),
+               "ds rows_forward");
+        DS_TRY(phi::ds_cols(D, 0, tn, s), "ds cols");
+    }
+    DS_TRY(phi::ds_rows_inverse(D, phi::DsRowOut::Field, u, nullptr, nullptr, nullptr, 0.0, s), "ds rows_inverse");
+    return PHI_OK;
+}
 
 }  // namespace
 
@@ -202,7 +241,7 @@ phi_status phi_ds_create(const phi_params* solve, const phi_ds_options* opt, voi
         const size_t o_part = off;
         off = align256(off + 2 * phi::kDsReduceBlocks * sizeof(double));
         const size_t o_spec = off;
-        off = align256(off + 2 * nn * es);
+        off = align256(off + 2 * static_cast<size_t>(n) * (n + 64) * es);
         const size_t o_wc = off;
         off = align256(off + 2 * nn * es);
         const size_t o_r1 = off;
@@ -250,6 +289,7 @@ phi_status phi_ds_create(const phi_params* solve, const phi_ds_options* opt, voi
         d.twr = base + o_twr;
         d.twr_count = static_cast<int>(twr.size() / 2);
         d.spec = base + o_spec;
+        d.spec_stride = n + 64;
         d.partials = reinterpret_cast<double*>(base + o_part);
         ds->work_c = base + o_wc;
         ds->work_r1 = base + o_r1;
@@ -295,39 +335,11 @@ phi_status phi_ds_plan(phi_ds_t ds, phi_plan_t* plan) {
 }
 
 phi_status phi_ds_forward(phi_ds_t ds, void* u, int32_t steps, void* v_store, void* phi_store, void* stream) {
-    phi_status st = check(ds);
-    if (st != PHI_OK) return st;
-    if (!u || steps < 0) return err(PHI_ERR_INVALID_ARG, "NULL field or negative step count");
-    if (steps == 0) return PHI_OK;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const phi::DsDev& D = ds->dev;
-    const size_t nn = static_cast<size_t>(ds->n) * ds->n;
-    const int K = static_cast<int>(ds->non.size());
-    const int total = steps * K;
-    char* vs = static_cast<char*>(v_store);
-    char* ps = static_cast<char*>(phi_store);
-    // the first linear substep; then per nonlinear substep: complete the linear
-    // substep (v_k, rho_k), Phi_k, the nonlinear substep fused into the next
-    // linear substep (consecutive linear substeps of two steps merged)
-    const int t0 = ds->lin_first_table;
-    DS_TRY(phi::ds_rows_forward(D, phi::DsRowIn::Plain, 0, t0, u, nullptr, nullptr, nullptr, nullptr, 0.0, s),
-           "ds rows_forward");
-    DS_TRY(phi::ds_cols(D, 0, t0, s), "ds cols");
-    for (int k = 0; k < total; ++k) {
-        const double ntau = ds->non[k % K] * ds->tau;
-        void* v = vs ? static_cast<void*>(vs + static_cast<size_t>(k) * nn * 2 * ds->elem) : ds->work_c;
-        void* pot = ps ? static_cast<void*>(ps + static_cast<size_t>(k) * nn * ds->elem) : ds->work_r2;
-        DS_TRY(phi::ds_rows_inverse(D, phi::DsRowOut::Density, v, ds->work_r1, nullptr, nullptr, ntau, s),
-               "ds rows_inverse");
-        st = solve_potential(ds, ds->work_r1, pot, false, stream);
-        if (st != PHI_OK) return st;
-        const int tn = table_after(ds, k, total);
-        DS_TRY(phi::ds_rows_forward(D, phi::DsRowIn::Nonlinear, 0, tn, v, nullptr, pot, nullptr, nullptr, ntau, s),
-               "ds rows_forward");
-        DS_TRY(phi::ds_cols(D, 0, tn, s), "ds cols");
-    }
-    DS_TRY(phi::ds_rows_inverse(D, phi::DsRowOut::Field, u, nullptr, nullptr, nullptr, 0.0, s), "ds rows_inverse");
-    return PHI_OK;
+    return forward(ds, u, steps, v_store, phi_store, false, stream);
+}
+
+phi_status phi_ds_forward_plain(phi_ds_t ds, void* u, int32_t steps, void* v_store, void* phi_store, void* stream) {
+    return forward(ds, u, steps, v_store, phi_store, true, stream);
 }
 
 phi_status phi_ds_backward(phi_ds_t ds, void* g, int32_t steps, const void* v_store, const void* phi_store,
@@ -357,7 +369,7 @@ phi_status phi_ds_backward(phi_ds_t ds, void* g, int32_t steps, const void* v_st
         const void* pot = ps + static_cast<size_t>(k) * nn * ds->elem;
         DS_TRY(phi::ds_rows_inverse(D, phi::DsRowOut::AdjointSource, ds->work_c, ds->work_r1, v, pot, ntau, s),
                "ds rows_inverse");
-        st = solve_potential(ds, ds->work_r1, ds->work_r2, true, stream);
+        st = solve_potential(ds, ds->work_r1, ds->work_r2, true, false, stream);
         if (st != PHI_OK) return st;
         const int tp = (k > 0) ? table_after(ds, k - 1, total) : ds->lin_first_table;
         DS_TRY(phi::ds_rows_forward(D, phi::DsRowIn::Adjoint, 1, tp, ds->work_c, v, pot, ds->work_r1, ds->work_r2,

@@ -24,12 +24,14 @@
 #include "ds_kernels.hpp"
 #include "solver_device.hpp"
 
+
 namespace phi {
 
 namespace {
 
-// Rows per block of the row passes: as many as fit 1024 threads and about
-// 70 KB of LDS, a power of two (so it divides N).
+// Rows per block of the row passes: as many as fit 1024 threads and 70
+// KB of LDS, a power of two (so it divides N), halved while the N rows make fewer
+// than 256 blocks (one per CU) and a block has more than one wave.
 template <typename R, int LOG>
 constexpr int ds_rows_per_block() {
     constexpr int nt = FftShape<LOG>::NT;
@@ -39,15 +41,17 @@ constexpr int ds_rows_per_block() {
     lim = lim < (1 << LOG) ? lim : (1 << LOG);
     int g = 1;
     while (2 * g <= lim) g *= 2;
+    while ((1 << LOG) / g < 256 && nt * g > 64) g /= 2;
     return g;
 }
 
-// Columns per block of the column pass: blocks of at least 256 threads, at
-// most the N columns there are.
+// Columns per block of the column pass: blocks of 256 threads where a transform
+// has fewer, halved in the same way, at most the N columns there are.
 template <int LOG>
 constexpr int ds_cols_per_block() {
     constexpr int nt = FftShape<LOG>::NT;
-    constexpr int g = nt >= 256 ? 1 : 256 / nt;
+    int g = nt >= 256 ? 1 : 256 / nt;
+    while ((1 << LOG) / g < 256 && nt * g > 64) g /= 2;
     return g < (1 << LOG) ? g : (1 << LOG);
 }
 
@@ -61,14 +65,69 @@ __device__ __forceinline__ cpx<R> mul_tab(cpx<R> x, cpx<R> m) {
     else return {x.x * m.x - x.y * m.y, x.x * m.y + x.y * m.x};
 }
 
-// e^{i phi} with phi = tau (c_l |v|^2 + c_p Phi)
+// phi = tau (c_l |v|^2 + c_p Phi)
 template <typename R>
-__device__ __forceinline__ cpx<R> nonlinear_rotation(cpx<R> v, R pot, R tau, R cl, R cp) {
+__device__ __forceinline__ R nonlinear_phase(cpx<R> v, R pot, R tau, R cl, R cp) {
     const R rho = v.x * v.x + v.y * v.y;
-    const R ph = tau * (cl * rho + cp * pot);
+    return tau * (cl * rho + cp * pot);
+}
+
+// e^{i phi} by the library, for any phase.
+template <typename R>
+__device__ __forceinline__ cpx<R> rotation(R ph) {
     R sn, cs;
     sin_cos(ph, &sn, &cs);
     return {cs, sn};
+}
+
+// e^{i phi} without a branch, for |phi| <= kDirectPhase; a larger (or NaN) phase
+// sets `large`, and the caller then takes the point again through rotation().
+// Reduction by the nearest multiple of pi/2 (pi/2 as two doubles, fused products:
+// exact to below rounding for these phases), Taylor polynomials on [-pi/4, pi/4].
+// FP64: to x^15 and x^16 (remainders 5e-17 and 2e-18).  FP32 runs in FP64, which
+// has the same rate here, to x^9 and x^10 (2e-9 and 2e-10), and rounds once.  The
+// library routines branch per call, and sixteen of them unrolled no longer fit the
+// instruction cache: the nonlinear row pass in FP64 15.3 -> 8.4 us at 512^2 (a
+// pass without rotations 7) and 48 -> 39.5 us at 2048^2.
+constexpr double kDirectPhase = 1.0e6;
+template <typename R>
+__device__ __forceinline__ cpx<R> rotation_direct(R phase, bool& large) {
+    const double ph = phase;
+    large = large || !(fabs(ph) <= kDirectPhase);
+    const double k = rint(ph * 0.63661977236758134308);          // 2 / pi
+    double r = fma(-k, 1.57079632679489661923, ph);              // pi/2 to a double
+    double p, q, cr;
+    const int n = static_cast<int>(k);                           // quadrant; k out of range: large
+    if constexpr (sizeof(R) == 8) {
+        r = fma(-k, 6.12323399573676588613e-17, r);              // and the rest
+        const double z = r * r;
+        p = fma(-1.0 / 1307674368000.0, z, 1.0 / 6227020800.0);  // (sin r - r) / r^3
+        p = fma(p, z, -1.0 / 39916800.0);
+        p = fma(p, z, 1.0 / 362880.0);
+        p = fma(p, z, -1.0 / 5040.0);
+        p = fma(p, z, 1.0 / 120.0);
+        p = fma(p, z, -1.0 / 6.0);
+        q = fma(1.0 / 20922789888000.0, z, -1.0 / 87178291200.0);   // (cos r - 1 + r^2 / 2) / r^4
+        q = fma(q, z, 1.0 / 479001600.0);
+        q = fma(q, z, -1.0 / 3628800.0);
+        q = fma(q, z, 1.0 / 40320.0);
+        q = fma(q, z, -1.0 / 720.0);
+        q = fma(q, z, 1.0 / 24.0);
+        const double w = fma(-0.5, z, 1.0);                      // 1 - r^2/2, and what it rounds away
+        cr = w + fma(z * z, q, fma(-0.5, z, 1.0 - w));
+    } else {
+        const double z = r * r;
+        p = fma(1.0 / 362880.0, z, -1.0 / 5040.0);
+        p = fma(p, z, 1.0 / 120.0);
+        p = fma(p, z, -1.0 / 6.0);
+        q = fma(-1.0 / 3628800.0, z, 1.0 / 40320.0);
+        q = fma(q, z, -1.0 / 720.0);
+        q = fma(q, z, 1.0 / 24.0);
+        cr = fma(z * z, q, fma(-0.5, z, 1.0));
+    }
+    const double sr = fma(p * (r * r), r, r);
+    const double sn = (n & 1) ? cr : sr, cs = (n & 1) ? sr : cr;
+    return {static_cast<R>(((n + 1) & 2) ? -cs : cs), static_cast<R>((n & 2) ? -sn : sn)};
 }
 
 template <typename R, int LOG, int MODE, bool CONJ>
@@ -89,24 +148,34 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * ds_rows_per_block<R, LOG>())) 
     const size_t base = static_cast<size_t>(row0 + g) * N;
     const R tau = ntau, cl = static_cast<R>(D.c_local), cp = static_cast<R>(D.c_potential);
     cpx<R> a[16];
-    if constexpr (MODE == static_cast<int>(DsRowIn::Adjoint)) {
-        // adjoint of the nonlinear substep: g e^{-i phi} + 2 tau (c_l q + c_p t) v.
-        // Five inputs and a sine/cosine per point: all 16 points at once need more
-        // registers than a SIMD holds for two waves (FP64) or four (FP32), so the
-        // points go four at a time through a loop that is not unrolled, each result
-        // parked in this thread's own slots of the transform buffer (read back by
-        // the same thread only, before the transform's first barrier).
+    bool large = false;
+    // one point's input, with its rotation e
+    auto point = [&](size_t idx, cpx<R> xv, auto&& turn) {
+        if constexpr (MODE == static_cast<int>(DsRowIn::Adjoint)) {
+            // adjoint of the nonlinear substep: g e^{-i phi} + 2 tau (c_l q + c_p t) v
+            const cpx<R> vv = v[idx];
+            const cpx<R> e = turn(nonlinear_phase(vv, pot[idx], tau, cl, cp));
+            const R r = R(2) * tau * (cl * s[idx] + cp * t[idx]);
+            return cpx<R>{xv.x * e.x + xv.y * e.y + r * vv.x, xv.y * e.x - xv.x * e.y + r * vv.y};
+        } else {
+            return cmul(xv, turn(nonlinear_phase(xv, pot[idx], tau, cl, cp)));
+        }
+    };
+    const auto direct = [&](R ph) { return rotation_direct(ph, large); };
+    // Inputs and a sine/cosine per point: all 16 points at once need more
+    // registers than a SIMD holds for two waves (FP64, the adjoint's five inputs) or
+    // four (FP32, whose rotations run in FP64), so the points go four at a time
+    // through a loop that is not unrolled, each result parked in this thread's own
+    // slots of the transform buffer (read back by the same thread only, before the
+    // transform's first barrier).
+    if constexpr (MODE == static_cast<int>(DsRowIn::Adjoint) ||
+                  (MODE == static_cast<int>(DsRowIn::Nonlinear) && sizeof(R) == 4)) {
 #pragma unroll 1
         for (int c = 0; c < 16; c += 4) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const size_t idx = base + tid + NT * (c + j);
-                const cpx<R> xv = x[idx];
-                const cpx<R> vv = v[idx];
-                const cpx<R> e = nonlinear_rotation(vv, pot[idx], tau, cl, cp);
-                const R r = R(2) * tau * (cl * s[idx] + cp * t[idx]);
-                lds[lds_pad(tid + NT * (c + j))] = {xv.x * e.x + xv.y * e.y + r * vv.x,
-                                                    xv.y * e.x - xv.x * e.y + r * vv.y};
+                lds[lds_pad(tid + NT * (c + j))] = point(idx, x[idx], direct);
             }
         }
 #pragma unroll
@@ -117,7 +186,20 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * ds_rows_per_block<R, LOG>())) 
             const size_t idx = base + tid + NT * i;
             const cpx<R> xv = x[idx];
             if constexpr (MODE == static_cast<int>(DsRowIn::Plain)) a[i] = xv;
-            else a[i] = cmul(xv, nonlinear_rotation(xv, pot[idx], tau, cl, cp));
+            else if constexpr (MODE == static_cast<int>(DsRowIn::NonlinearLibrary))
+                a[i] = point(idx, xv, [](R ph) { return rotation(ph); });
+            else a[i] = point(idx, xv, direct);
+        }
+    }
+    if constexpr (MODE == static_cast<int>(DsRowIn::Nonlinear) || MODE == static_cast<int>(DsRowIn::Adjoint)) {
+        if (large) {   // some phase beyond the direct range: this thread's points again
+#pragma unroll 1
+            for (int i = 0; i < 16; ++i) {
+                const size_t idx = base + tid + NT * i;
+                lds[lds_pad(tid + NT * i)] = point(idx, x[idx], [](R ph) { return rotation(ph); });
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) a[i] = lds[lds_pad(tid + NT * i)];
         }
     }
     fft_reg<R, LOG, -1>(a, lds, tw, tid);
@@ -134,7 +216,7 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * ds_rows_per_block<R, LOG>())) 
         const int idx = threadIdx.x + k * NT * G;
         const int gg = idx % G;
         const int m = idx / G;
-        spec[static_cast<size_t>(m) * N + row0 + gg] = lds_all[gg * LP + lds_pad(m)];
+        spec[static_cast<size_t>(m) * D.spec_stride + row0 + gg] = lds_all[gg * LP + lds_pad(m)];
     }
 }
 
@@ -153,7 +235,7 @@ __global__ __launch_bounds__(FftShape<LOG>::NT * ds_cols_per_block<LOG>()) void 
     const int m = blockIdx.x * G + g;
     const bool active = m < N;
     // idle lanes of the last block read column N - 1 and never store
-    cpx<R>* col = static_cast<cpx<R>*>(D.spec) + static_cast<size_t>(active ? m : N - 1) * N;
+    cpx<R>* col = static_cast<cpx<R>*>(D.spec) + static_cast<size_t>(active ? m : N - 1) * D.spec_stride;
     cpx<R> a[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) a[i] = col[tid + NT * i];
@@ -188,7 +270,7 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * ds_rows_per_block<R, LOG>())) 
         const int idx = threadIdx.x + k * NT * G;
         const int gg = idx % G;
         const int m = idx / G;
-        lds_all[gg * LP + lds_pad(m)] = spec[static_cast<size_t>(m) * N + row0 + gg];
+        lds_all[gg * LP + lds_pad(m)] = spec[static_cast<size_t>(m) * D.spec_stride + row0 + gg];
     }
     __syncthreads();
     cpx<R> a[16];
@@ -198,6 +280,7 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * ds_rows_per_block<R, LOG>())) 
     const R scale = static_cast<R>(1.0 / (static_cast<double>(N) * N));
     const R tau = ntau, cl = static_cast<R>(D.c_local), cp = static_cast<R>(D.c_potential);
     const size_t base = static_cast<size_t>(row0 + g) * N;
+    bool large = false;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const size_t idx = base + tid + NT * i;
@@ -208,8 +291,20 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * ds_rows_per_block<R, LOG>())) 
         } else if constexpr (MODE == static_cast<int>(DsRowOut::AdjointSource)) {
             // s = -Im(conj(g) w), w = v e^{i phi}: the nonlinear substep's output
             const cpx<R> vv = v[idx];
-            const cpx<R> w = cmul(vv, nonlinear_rotation(vv, pot[idx], tau, cl, cp));
+            const cpx<R> w = cmul(vv, rotation_direct(nonlinear_phase(vv, pot[idx], tau, cl, cp), large));
             out_r[idx] = -(f.x * w.y - f.y * w.x);
+        }
+    }
+    if constexpr (MODE == static_cast<int>(DsRowOut::AdjointSource)) {
+        if (large) {   // some phase beyond the direct range: this thread's points again
+#pragma unroll 1
+            for (int i = 0; i < 16; ++i) {
+                const size_t idx = base + tid + NT * i;
+                const cpx<R> f = out_c[idx];
+                const cpx<R> vv = v[idx];
+                const cpx<R> w = cmul(vv, rotation(nonlinear_phase(vv, pot[idx], tau, cl, cp)));
+                out_r[idx] = -(f.x * w.y - f.y * w.x);
+            }
         }
     }
 }
@@ -317,6 +412,10 @@ hipError_t rows_forward_log(const DsDev& D, DsRowIn mode, int conj, const void* 
         return launch_rows_forward<R, LOG, 0, true>(D, x, v, pot, s, t, ex, ntau, st);
     if (mode == DsRowIn::Nonlinear && !conj)
         return launch_rows_forward<R, LOG, 1, false>(D, x, v, pot, s, t, ex, ntau, st);
+    if constexpr (sizeof(R) == 4) {
+        if (mode == DsRowIn::NonlinearLibrary && !conj)
+            return launch_rows_forward<R, LOG, 3, false>(D, x, v, pot, s, t, ex, ntau, st);
+    }
     if (mode == DsRowIn::Adjoint && conj)
         return launch_rows_forward<R, LOG, 2, true>(D, x, v, pot, s, t, ex, ntau, st);
     return hipErrorInvalidValue;

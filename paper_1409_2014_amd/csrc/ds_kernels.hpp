@@ -24,6 +24,8 @@ struct DsDev {
     const void* twr;       // register-FFT stage twiddles of length N
     int twr_count;
     void* spec;            // N x N complex, column-major [kx][y]: the field after the x transform
+    int spec_stride = 0;    // elements between its columns (N + 64: a power of two would put a row
+                            // block's writes, one per column, into a few cache sets)
     double* partials;      // kDsReduceBlocks x 2 FP64 partial sums of the moments
 };
 
@@ -34,6 +36,7 @@ enum class DsRowIn {
     Plain = 0,       // x = u
     Nonlinear = 1,   // x = v e^{i phi}, phi = s (c_l |v|^2 + c_p Phi)
     Adjoint = 2,     // x = g e^{-i phi} + 2 s (c_l q + c_p t) v
+    NonlinearLibrary = 3,   // Nonlinear with the library's sine and cosine
 };
 // Outputs of the row pass that completes a linear substep.
 enum class DsRowOut {

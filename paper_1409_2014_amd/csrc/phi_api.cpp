@@ -223,6 +223,7 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
     d->n_nodes = hp.n_nodes;
     d->component = hp.component;
     d->partition_erfc = hp.partition_erfc;
+    d->plain = 0;
     d->inv_sigma = 1.0 / hp.sigma;
     // The two branches of a solve share the GPU, and the one enqueued first is
     // served first: the node-side chain (the same few small kernels at every N)
@@ -462,6 +463,23 @@ void push_items(std::vector<phi::WorkItem>* v, int member, int kind, int from, i
 }
 
 }  // namespace
+
+phi_status phi::solve_plain(phi_plan_t plan, const void* in, void* out, void* stream) {
+    phi_status st = check_plan(plan);
+    if (st != PHI_OK) return st;
+    if (plan->n_members > 0 || plan->host.dtype != PHI_F32) return run(plan, phi::Stage::Solve, in, out, 0, stream);
+    if (!in || !out) return fail(plan, PHI_ERR_INVALID_ARG, "NULL data pointer");
+    if (in == out) return fail(plan, PHI_ERR_INVALID_ARG, "input and output must not alias");
+    st = check_device(plan);
+    if (st != PHI_OK) return st;
+    phi::DevPlan d = plan->dev;
+    d.nd = d.nd_all;
+    d.pair_taps = 0;
+    d.plain = 1;
+    hipError_t e = phi::enqueue(d, plan->streams, phi::Stage::Solve, in, out, 0, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return device_fail(plan, e, "kernel launch");
+    return PHI_OK;
+}
 
 phi_status phi::thread_error(phi_status st, const std::string& msg) {
     g_thread_error = msg;

@@ -302,7 +302,9 @@ __device__ __forceinline__ constexpr R norm_loss() {
 //   1  -kx ky/|k|^2
 //   2  1/|k| with the Gaussian partition:  g1 = (1 - e^{-|k|^2/sigma^2}) / |k|
 //   3  1/|k| with the erfc partition:      g1 = erf(|k|/sigma) / |k|
+//   4, 5  as 0, 1 with the quotient from the tables in FP32 (plain arithmetic)
 constexpr int kKindQuadratic = 0, kKindMixed = 1, kKindCoulombGauss = 2, kKindCoulombErfc = 3;
+constexpr int kKindQuadraticPlain = 4, kKindMixedPlain = 5;
 
 // erf(x)/x for x >= 0, an even entire function: the series 2/sqrt(pi) (1 - x^2/3)
 // below a threshold where the next term (x^4/10) is below the precision's
@@ -391,7 +393,7 @@ __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base
         } else if constexpr (KIND == kKindCoulombErfc) {
             const R s2 = a + b;
             gfac = erf_over_x<R>(sqrt(s2), s2) * (inv_sigma * scale);
-        } else if constexpr (sizeof(R) == 4) {
+        } else if constexpr (sizeof(R) == 4 && (KIND == kKindQuadratic || KIND == kKindMixed)) {
             // the quotient of the integer frequency indices (exact products up to
             // 2^24), corrected by its remainder: within an ulp; A + B - A B as
             // A + B e^{-a}, rounded once
@@ -407,7 +409,7 @@ __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base
             gfac = fma(q, w, (q * norm_loss<R, LOG>()) * w);   // less than half an ulp: added before rounding
         } else {
             R num;
-            if constexpr (KIND == kKindMixed) {
+            if constexpr (KIND == kKindMixed || KIND == kKindMixedPlain) {
                 const int p = tid + NT * i;                 // frequency index along y, FFT order
                 const int ms = (p < HALF) ? p : p - F;      // p = F/2 (Nyquist) -> -F/2
                 num = (p == HALF) ? R(0) : fx * (static_cast<R>(ms) * fs);

@@ -204,6 +204,19 @@ hipError_t launch_cols_highfreq_dir(const DevPlan& P, hipStream_t s) {
     // (the DS, y and mixed multipliers), so a batch member and its single plan
     // run the same code; the Coulomb multipliers use the general bounds only
     const bool exact = 2 * P.n == P.n_fine;
+    if constexpr (sizeof(R) == 4 && DIR < 0) {
+        if (P.plain) {
+            if (P.component == 2 && exact)
+                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixedPlain, true>), dim3(grid), dim3(block), 0, s, P);
+            else if (P.component == 2)
+                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixedPlain, false>), dim3(grid), dim3(block), 0, s, P);
+            else if (exact)
+                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindQuadraticPlain, true>), dim3(grid), dim3(block), 0, s, P);
+            else
+                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindQuadraticPlain, false>), dim3(grid), dim3(block), 0, s, P);
+            return hipGetLastError();
+        }
+    }
     if (P.component == 2 && exact)
         PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixed, true>), dim3(grid), dim3(block), 0, s, P);
     else if (P.component == 2)

@@ -32,6 +32,7 @@ struct DevPlan {
     int partition_erfc;     // Coulomb: partition erfc(|k|/sigma) (else e^{-|k|^2/sigma^2})
     double inv_sigma;       // 1 / sigma
     int highfreq_first;     // a solve enqueues the I1 columns before the node-side chain
+    int plain;              // FP32: a solve in its plain arithmetic (solve_plain)
     int shared;             // one stream: the type-1 window columns and all I1 columns in one launch
     double freq_scale;      // 1 / (n_fine h sigma): k/sigma per fine-grid frequency index
     int col_stride;         // elements between consecutive columns of xt and tt (N + pad)

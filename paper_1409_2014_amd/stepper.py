@@ -106,11 +106,14 @@ class DSStepper:
     def forward(self, u: torch.Tensor, steps: int, store=None) -> torch.Tensor:
         """Advances u in place by `steps` steps; fills `store` (from new_store)
         for a later reverse pass when given."""
+        return self._run("phi_ds_forward", u, steps, store)
+
+    def _run(self, name: str, u: torch.Tensor, steps: int, store) -> torch.Tensor:
         self._check_field(u, "u")
         v, p = (None, None) if store is None else store
         if store is not None and (v.shape[0] < steps * self.substeps or p.shape[0] < steps * self.substeps):
             raise ValueError("store holds fewer steps than requested")
-        self._call("phi_ds_forward", _ptr(u), int(steps), _ptr(v), _ptr(p))
+        self._call(name, _ptr(u), int(steps), _ptr(v), _ptr(p))
         return u
 
     def backward(self, g: torch.Tensor, steps: int, store) -> torch.Tensor:
@@ -150,7 +153,9 @@ class DSStepper:
         """J = h^2 sum |u(T)|^4 after `steps` steps from u0, and dJ/du0 by the
         reverse pass with checkpoints: the states at segment starts are kept,
         each segment but the last is run again with its store before its
-        reverse pass (the last keeps the store of the first run).
+        reverse pass (the last keeps the store of the first run).  The runs are
+        phi_ds_forward_plain's: an FP32 loss, an FP64 number, does not depend on
+        the kernels a size selects.
 
         Returns (J as a 0-d float64 device tensor, gradient, counts of forward,
         recomputed and transposed potential solves: substeps per step each)."""
@@ -160,14 +165,14 @@ class DSStepper:
         starts = []
         for k, m in enumerate(lens):
             starts.append(u.clone())
-            self.forward(u, m, store if k == len(lens) - 1 else None)
+            self._run("phi_ds_forward_plain", u, m, store if k == len(lens) - 1 else None)
         loss = self.moments(u)[1]
         g = self.loss_grad(u)
         recomputed = 0
         for k in range(len(lens) - 1, -1, -1):
             if k != len(lens) - 1:
                 w = starts[k].clone()
-                self.forward(w, lens[k], store)
+                self._run("phi_ds_forward_plain", w, lens[k], store)
                 recomputed += lens[k]
             self.backward(g, lens[k], store)
         k = self.substeps
