@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kBatchThreads) void kb_cols_type1(BatchDev B) {
     const WorkItem w = B.cols1[blockIdx.x];
     const DevPlan P = B.members[w.member];
     PHI_BATCH_LOG(P.log_fine,
-                  (cols_type1_body<R, LOG_, DIR, batch_lines(LOG_), batch_lines(LOG_), false>(P, w.item, lds_all)));
+                  (cols_type1_body<R, LOG_, DIR, batch_lines(LOG_), batch_type1_cols(LOG_), false>(P, w.item, lds_all)));
 }
 
 template <typename R, int DIR>

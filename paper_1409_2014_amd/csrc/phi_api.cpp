@@ -650,7 +650,7 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
             push_items(hp.component == 2 ? &cols_mixed : &cols, i, 0, 0, hp.n_fine / 2 + 1, g);
             push_items(&cols_t2, i, 1, hp.half.col_lo, hp.half.col_hi, g);
             push_items(hp.half.grouped ? &nodes : &nodes_gen, i, 0, 0, hp.half.n_sub, 1);
-            push_items(&cols1, i, 0, hp.half.col_lo, hp.half.col_hi, g);
+            push_items(&cols1, i, 0, hp.half.col_lo, hp.half.col_hi, phi::batch_type1_cols(hp.log_fine));
         }
         // one allocation: table sets, member workspaces, device views, work tables
         Layout L;

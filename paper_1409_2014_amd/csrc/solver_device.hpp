@@ -867,13 +867,13 @@ __device__ __forceinline__ void nodes_group_body(const DevPlan& P, int sidx, Nod
 // cols_type1: sum the spread tiles onto one window column, FFT along y (only
 // the Q window inputs are non-zero), keep the N centred rows, times d(n2)
 // ---------------------------------------------------------------------------
-// A block transforms COLS window columns (COLS = 1 or G).  Window cell
+// A block transforms COLS window columns (COLS divides G).  Window cell
 // (i1, i2) is the sum of the tile entries listed for it, in list order: 4
 // lanes split the list, then a fixed shuffle tree; all threads of the block
 // share the cells of its columns, so with COLS = 1 the length of the lists
 // (set by the node count, not by N) is spread over a whole block at every
 // grid size.  Column c is staged in group c's buffer; group g transforms
-// column g % COLS (with COLS = 1 every group runs the same transform, which the
+// column g % COLS (with COLS < G the other groups repeat a transform, which the
 // block's barriers need anyway) and groups g < COLS store.
 template <typename R, int LOG, int DIR, int G, int COLS, bool EXACT>
 __device__ __forceinline__ void cols_type1_body(const DevPlan& P, int i1_base, cpx<R>* lds_all) {
@@ -883,7 +883,7 @@ __device__ __forceinline__ void cols_type1_body(const DevPlan& P, int i1_base, c
     constexpr int BT = NT * G;
     constexpr int L = 4;
     constexpr int LP = lds_group_stride(F);
-    static_assert(COLS == 1 || COLS == G, "one column per block or one per group");
+    static_assert(COLS >= 1 && G % COLS == 0, "whole rounds of the groups");
     static_assert(BT % L == 0, "the block splits into whole lane groups");
     const int g = threadIdx.x / NT;
     const int tid = threadIdx.x - g * NT;

@@ -140,6 +140,14 @@ constexpr int batch_lines(int log_fine) {
     return nt >= kBatchThreads ? 1 : kBatchThreads / nt;
 }
 
+// Type-1 window columns per batched block: at most 4.  The gather of a window
+// cell is a chain of dependent loads, so a batch of few small members is bound by
+// the blocks in flight: 24 members of sides 66 to 300 in FP32 take 69.6 us with 4
+// against 83.5 with the 8 or 16 transforms a block holds, 12 of 66 to 512 in FP64
+// 70.0 against 85.8.  Fewer than 4 cost a full chip its repeated transforms (64
+// members of 128 to 1024 in FP32: 298, 293, 290 us with 1, 2, 4; 288 with all).
+constexpr int batch_type1_cols(int log_fine) { return batch_lines(log_fine) < 4 ? batch_lines(log_fine) : 4; }
+
 struct WorkItem {
     int member;   // index into BatchDev::members
     int item;     // first grid row, spectrum / window column, or subproblem
