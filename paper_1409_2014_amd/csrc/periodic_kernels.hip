@@ -26,10 +26,27 @@ namespace phi {
 
 namespace {
 
-// Row pairs per block: the same budget as the padded row kernels, whose
-// transform length 2^LOG also serves 2^LOG / 2 row pairs here.
+// Row pairs per block, halved from the padded row kernels' budget until every CU
+// has a block or the block is one wave; columns per block likewise, from blocks of
+// 256 threads.  The small and middle grids are bound by the blocks in flight: with
+// the whole budget 512^2 rows fill 16 (FP32) or 32 (FP64) of the 256 CUs.  Measured
+// per solve, whole budget against this: 256^2 FP32 18.5 and 13.9 us, 512^2 FP32 22.6
+// and 16.4, FP64 24.3 and 19.0, 1024^2 FP32 26.6 and 21.1, FP64 32.6 and 29.0.
+// Halving to 128 blocks leaves 1024^2 at 23.7 and 33.0, to 512 at 21.4 and 30.4 (the
+// spectrum is stored in shorter runs); from 2048^2 on the budget fills the chip.
 template <typename R, int LOG>
-constexpr int pairs_per_block() { return rows_per_block<R, LOG>(); }
+constexpr int pairs_per_block() {
+    int g = rows_per_block<R, LOG>();
+    while ((1 << LOG) / 2 / g < 256 && FftShape<LOG>::NT * g > 64) g /= 2;
+    return g;
+}
+
+template <int LOG>
+constexpr int per_cols_per_block() {
+    int g = lines_per_block<LOG>();
+    while ((1 << LOG) / 2 / g < 256 && FftShape<LOG>::NT * g > 64) g /= 2;
+    return g;
+}
 
 template <typename R, int LOG>
 __global__ __launch_bounds__((FftShape<LOG>::NT * pairs_per_block<R, LOG>())) void k_per_rows_forward(
@@ -73,11 +90,11 @@ __global__ __launch_bounds__((FftShape<LOG>::NT * pairs_per_block<R, LOG>())) vo
 
 // COMP: 0 -kx^2/|k|^2, 1 -ky^2/|k|^2, 2 -kx ky/|k|^2
 template <typename R, int LOG, int COMP>
-__global__ __launch_bounds__(FftShape<LOG>::NT * lines_per_block<LOG>()) void k_per_cols(DevPlan P) {
+__global__ __launch_bounds__(FftShape<LOG>::NT * per_cols_per_block<LOG>()) void k_per_cols(DevPlan P) {
     using Sh = FftShape<LOG>;
     constexpr int N = Sh::F;
     constexpr int NT = Sh::NT;
-    constexpr int G = lines_per_block<LOG>();
+    constexpr int G = per_cols_per_block<LOG>();
     __shared__ cpx<R> lds_all[G * lds_group_stride(N)];
     const int g = threadIdx.x / NT;
     const int tid = threadIdx.x - g * NT;
@@ -160,7 +177,7 @@ hipError_t periodic_log(const DevPlan& P, const void* in, void* out, hipStream_t
     constexpr int N = 1 << LOG;
     if (P.n != N || P.twn_count != FftShape<LOG>::tw_size()) return hipErrorInvalidValue;
     constexpr int GR = pairs_per_block<R, LOG>();
-    constexpr int GC = lines_per_block<LOG>();
+    constexpr int GC = per_cols_per_block<LOG>();
     constexpr int NT = FftShape<LOG>::NT;
     hipError_t e = mark_kernel(timer, "per_rows_forward", false, s);
     if (e != hipSuccess) return e;
