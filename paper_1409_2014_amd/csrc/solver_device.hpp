@@ -319,6 +319,72 @@ __device__ __forceinline__ R erf_over_x(R x, R x2) {
     }
 }
 
+// The multiplier g1 along spectrum column m1.
+// g1 = -(k_a k_b/|k|^2) (1 - e^{-|k|^2/sigma^2}) / F^2 with a = kx^2/sigma^2,
+// b = ky^2/sigma^2 and 1 - e^{-(a+b)} = A + B - A B, A = 1 - e^{-a},
+// B = 1 - e^{-b} (all terms >= 0); branch-free per point, g1(0) = 0.  The
+// numerator is a or b, or for the mixed component (kx/sigma)(ky/sigma) with
+// the signed frequency index of the point.
+// The mixed numerator is odd in each frequency, and a bin on a Nyquist line
+// (|index| = F/2) stands for +k and -k: it takes the mean of the multiplier
+// over them, 0 (also at the corner).
+template <typename R, int LOG, int KIND>
+struct ColumnFactor {
+    static constexpr int HALF = (1 << LOG) / 2;
+    R a, A, scale, fs, fx, inv_sigma;
+    bool ycomp;
+    // FP32: frequency index of the column (mx2 is positive at the origin too,
+    // where the numerator is 0; the mixed one is 0 on the Nyquist column), and A,
+    // 1 - A = e^{-a} with the sign and the power of two 1 / F^2
+    R mxn, mx2, part_a, part_e;
+
+    __device__ __forceinline__ ColumnFactor(const DevPlan& P, int m1) {
+        a = static_cast<R>(P.gx[2 * m1]);
+        A = static_cast<R>(P.gx[2 * m1 + 1]);
+        scale = static_cast<R>(P.inv_f2);
+        ycomp = P.component == 1;
+        fs = static_cast<R>(P.freq_scale);
+        fx = (m1 == HALF) ? R(0) : static_cast<R>(m1) * fs;
+        inv_sigma = static_cast<R>(P.inv_sigma);
+        mxn = m1 == HALF ? R(0) : static_cast<R>(m1);
+        mx2 = static_cast<R>(m1) * static_cast<R>(m1) + tiny_normal<R>();
+        part_a = static_cast<R>(-P.gx[2 * m1 + 1] * P.inv_f2);
+        part_e = static_cast<R>((P.gx[2 * m1 + 1] - 1.0) * P.inv_f2);
+    }
+
+    // at signed frequency index my along y (nyquist: my = -F/2), (b, B) its table entry
+    __device__ __forceinline__ R at(R my, bool nyquist, R b, R B) const {
+        if constexpr (KIND == kKindCoulombGauss) {
+            // (1 - e^{-(a+b)}) / (sigma sqrt(a+b)): 0 * finite at k = 0
+            const R s2 = a + b + tiny_normal<R>();
+            return (A + B - A * B) * (inv_sigma * scale) / sqrt(s2);
+        } else if constexpr (KIND == kKindCoulombErfc) {
+            const R s2 = a + b;
+            return erf_over_x<R>(sqrt(s2), s2) * (inv_sigma * scale);
+        } else if constexpr (sizeof(R) == 4 && (KIND == kKindQuadratic || KIND == kKindMixed)) {
+            // the quotient of the integer frequency indices (exact products up to
+            // 2^24), corrected by its remainder: within an ulp; A + B - A B as
+            // A + B e^{-a}, rounded once
+            const R den = fma(my, my, mx2);
+            R num;
+            if constexpr (KIND == kKindMixed) num = nyquist ? R(0) : mxn * my;
+            else num = ycomp ? my * my : mx2;
+            const R r = __builtin_amdgcn_rcpf(den);
+            const R q0 = num * r;
+            const R q = fma(fma(-q0, den, num), r, q0);
+            const R w = fma(B, part_e, part_a);
+            return fma(q, w, (q * norm_loss<R, LOG>()) * w);   // less than half an ulp: added before rounding
+        } else {
+            R num;
+            if constexpr (KIND == kKindMixed || KIND == kKindMixedPlain) num = nyquist ? R(0) : fx * (my * fs);
+            else num = ycomp ? b : a;
+            // den = 0 only at k = 0, where num = 0: the quotient is 0 there
+            const R den = a + b + tiny_normal<R>();
+            return -(num * recip(den)) * (A + B - A * B) * scale;
+        }
+    }
+};
+
 template <typename R, int LOG, int DIR, int G, int KIND, bool EXACT>
 __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base, cpx<R>* lds_all) {
     using Sh = FftShape<LOG>;
@@ -357,70 +423,12 @@ __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base
     cpx<R> gb[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) gb[i] = gyr[tid + NT * i];
-    // g1 = -(k_a k_b/|k|^2) (1 - e^{-|k|^2/sigma^2}) / F^2 with a = kx^2/sigma^2,
-    // b = ky^2/sigma^2 and 1 - e^{-(a+b)} = A + B - A B, A = 1 - e^{-a},
-    // B = 1 - e^{-b} (all terms >= 0); branch-free per point, g1(0) = 0.  The
-    // numerator is a or b, or for the mixed component (kx/sigma)(ky/sigma) with
-    // the signed frequency index of the point.
-    // The mixed numerator is odd in each frequency, and a bin on a Nyquist line
-    // (|index| = F/2) stands for +k and -k: it takes the mean of the multiplier
-    // over them, 0 (also at the corner).
-    const int mc = active ? m1 : HALF;
-    const R a = static_cast<R>(P.gx[2 * mc]);
-    const R A = static_cast<R>(P.gx[2 * mc + 1]);
-    const R scale = static_cast<R>(P.inv_f2);
-    const bool ycomp = P.component == 1;
-    const R fs = static_cast<R>(P.freq_scale);
-    const R fx = (mc == HALF) ? R(0) : static_cast<R>(mc) * fs;
-    const R inv_sigma = static_cast<R>(P.inv_sigma);
-    // FP32: frequency indices of this thread's points (mx2 is positive at the
-    // origin too, where the numerator is 0; the mixed one is 0 on the Nyquist
-    // column), and A, 1 - A = e^{-a} with the sign and the power of two 1 / F^2
+    const ColumnFactor<R, LOG, KIND> factor(P, active ? m1 : HALF);
     const R fy = static_cast<R>(tid);
-    const R mxn = mc == HALF ? R(0) : static_cast<R>(mc);
-    const R mx2 = static_cast<R>(mc) * static_cast<R>(mc) + tiny_normal<R>();
-    const R part_a = static_cast<R>(-P.gx[2 * mc + 1] * P.inv_f2);
-    const R part_e = static_cast<R>((P.gx[2 * mc + 1] - 1.0) * P.inv_f2);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const R b = gb[i].x;
-        const R B = gb[i].y;
-        R gfac;
-        if constexpr (KIND == kKindCoulombGauss) {
-            // (1 - e^{-(a+b)}) / (sigma sqrt(a+b)): 0 * finite at k = 0
-            const R s2 = a + b + tiny_normal<R>();
-            gfac = (A + B - A * B) * (inv_sigma * scale) / sqrt(s2);
-        } else if constexpr (KIND == kKindCoulombErfc) {
-            const R s2 = a + b;
-            gfac = erf_over_x<R>(sqrt(s2), s2) * (inv_sigma * scale);
-        } else if constexpr (sizeof(R) == 4 && (KIND == kKindQuadratic || KIND == kKindMixed)) {
-            // the quotient of the integer frequency indices (exact products up to
-            // 2^24), corrected by its remainder: within an ulp; A + B - A B as
-            // A + B e^{-a}, rounded once
-            const R my = fy + static_cast<R>(NT * i - (i < 8 ? 0 : F));
-            const R den = fma(my, my, mx2);
-            R num;
-            if constexpr (KIND == kKindMixed) num = (i == 8 && tid == 0) ? R(0) : mxn * my;
-            else num = ycomp ? my * my : mx2;
-            const R r = __builtin_amdgcn_rcpf(den);
-            const R q0 = num * r;
-            const R q = fma(fma(-q0, den, num), r, q0);
-            const R w = fma(B, part_e, part_a);
-            gfac = fma(q, w, (q * norm_loss<R, LOG>()) * w);   // less than half an ulp: added before rounding
-        } else {
-            R num;
-            if constexpr (KIND == kKindMixed || KIND == kKindMixedPlain) {
-                const int p = tid + NT * i;                 // frequency index along y, FFT order
-                const int ms = (p < HALF) ? p : p - F;      // p = F/2 (Nyquist) -> -F/2
-                num = (p == HALF) ? R(0) : fx * (static_cast<R>(ms) * fs);
-            } else {
-                num = ycomp ? b : a;
-            }
-            // den = 0 only at k = 0, where num = 0: the quotient is 0 there
-            const R den = a + b + tiny_normal<R>();
-            gfac = -(num * recip(den)) * (A + B - A * B) * scale;
-        }
-        v[i] = cscale(v[i], gfac);
+        const R my = fy + static_cast<R>(NT * i - (i < 8 ? 0 : F));
+        v[i] = cscale(v[i], factor.at(my, i == 8 && tid == 0, gb[i].x, gb[i].y));
     }
     fft_reg<R, LOG, -DIR>(v, lds, tw, tid);
     if (active) {
@@ -432,6 +440,81 @@ __device__ __forceinline__ void cols_highfreq_body(const DevPlan& P, int m1_base
                 if (p < half) out[p] = v[i];
             } else if (i >= 12) {
                 if (p >= F - half) out[p - F] = v[i];
+            }
+        }
+    }
+}
+
+// The same column in two transforms of F/2 points, for F = 8192.  The data has at
+// most F/2 points, so its even frequencies are the F/2-point transform of x and the
+// odd ones that of x e^{DIR 2 pi i n / F}, without sums between the two; each half
+// goes through its own multiplier and inverse transform, and the column is the even
+// result plus e^{-DIR 2 pi i n / F} times the odd one.  8192 = 16^3 2 takes three
+// exchanges and a radix-2 stage per transform, 4096 = 16^3 two: a third less through
+// LDS, and a quarter of the LDS per wave.  The halves run one after the other (x is
+// read again), so one half's 16 points and the even result are held at a time.
+// The e^{-2 pi i k / F} are the last stage's twiddles of the F-point table, whose
+// earlier stages are the F/2-point table.  The column launch of a solve, before and
+// after: 3000^2 FP32 183 and 129 us, 4096^2 FP32 195 and 134, FP64 261 and 228, FP64
+// Coulomb at 3000^2 369 and 318.  (Both halves held at once, or their table reads
+// hoisted together, take 170 to 250 registers and cost more than they save.)
+template <typename R, int LOG, int DIR, int KIND, bool EXACT>
+__device__ __forceinline__ void cols_highfreq_halves_body(const DevPlan& P, int m1, cpx<R>* lds) {
+    using Sh = FftShape<LOG>;
+    using Hs = FftShape<LOG - 1>;
+    static_assert(Sh::REM == 1 && Sh::tw_offset(Sh::NSTAGE - 1) == Hs::tw_size(), "shared tables");
+    constexpr int F = Sh::F;
+    constexpr int H = F / 2;
+    constexpr int NT = Hs::NT;
+    int tid = threadIdx.x;
+    const cpx<R>* tw = static_cast<const cpx<R>*>(P.twr);
+    const cpx<R>* turn = tw + Hs::tw_size();   // e^{-2 pi i k / F}, k = 0 .. H - 1
+    const cpx<R>* gyr = static_cast<const cpx<R>*>(P.gyr);
+    const int half = EXACT ? F / 4 : (P.n >> 1);
+    cpx<R>* base = static_cast<cpx<R>*>(P.xt) + static_cast<size_t>(m1) * P.col_stride + half;
+    const ColumnFactor<R, LOG, KIND> factor(P, m1);
+    // slot i holds row n = p below F/4, n = p - H above: e^{.. n / F} = -e^{.. p / F} there
+    auto holds = [&](int i) { return EXACT || (i < 8 ? tid + NT * i < half : tid + NT * i >= H - half); };
+    cpx<R> even[16];
+#pragma unroll 1
+    for (int odd = 0; odd < 2; ++odd) {
+        // the thread's number is made opaque where a part begins: the tables are read
+        // there again, not held in registers through the parts before
+        asm volatile("" : "+v"(tid));
+        cpx<R> v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            v[i] = {R(0), R(0)};
+            if (holds(i)) v[i] = base[tid + NT * i - (i < 8 ? 0 : H)];
+        }
+        if (odd) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const cpx<R> t = turn[tid + NT * i];
+                v[i] = tw_mul<R, DIR>(v[i], i < 8 ? t : cpx<R>{-t.x, -t.y});
+            }
+        }
+        fft_reg<R, LOG - 1, DIR>(v, lds, tw, tid);
+        cpx<R> gb[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gb[i] = gyr[2 * (tid + NT * i) + odd];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const R my = static_cast<R>(2 * tid) + static_cast<R>(2 * NT * i + odd - (i < 8 ? 0 : F));
+            v[i] = cscale(v[i], factor.at(my, !odd && i == 8 && tid == 0, gb[i].x, gb[i].y));
+        }
+        asm volatile("" : "+v"(tid));
+        fft_reg<R, LOG - 1, -DIR>(v, lds, tw, tid);
+        asm volatile("" : "+v"(tid));
+        if (!odd) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) even[i] = v[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const cpx<R> t = turn[tid + NT * i];
+                const cpx<R> o = cadd(even[i], tw_mul<R, -DIR>(v[i], i < 8 ? t : cpx<R>{-t.x, -t.y}));
+                if (holds(i)) base[tid + NT * i - (i < 8 ? 0 : H)] = o;
             }
         }
     }

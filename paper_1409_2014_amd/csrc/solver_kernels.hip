@@ -83,6 +83,13 @@ __global__ __launch_bounds__(FftShape<LOG>::NT * lines_per_block<LOG>()) void k_
     cols_highfreq_body<R, LOG, DIR, G, KIND, EXACT>(P, xcd_logical_block(blockIdx.x, gridDim.x) * G, lds_all);
 }
 
+// four waves per SIMD in FP32, two in FP64: what the LDS buffers allow
+template <typename R, int LOG, int DIR, int KIND, bool EXACT>
+__global__ __launch_bounds__(FftShape<LOG>::NT / 2, sizeof(R) == 4 ? 4 : 2) void k_cols_highfreq_halves(DevPlan P) {
+    __shared__ cpx<R> lds[lds_group_stride((1 << LOG) / 2)];
+    cols_highfreq_halves_body<R, LOG, DIR, KIND, EXACT>(P, xcd_logical_block(blockIdx.x, gridDim.x), lds);
+}
+
 // one window column per block: the Q columns are few, so at small N blocks of
 // several columns would leave most of the chip idle on this critical path
 template <typename R, int LOG, int DIR>
@@ -194,42 +201,42 @@ hipError_t launch_rows_forward(const DevPlan& P, const void* rho, int dir, hipSt
     return dir < 0 ? launch_rows_forward_dir<R, LOG, -1>(P, src, s) : launch_rows_forward_dir<R, LOG, 1>(P, src, s);
 }
 
+// F = 8192 in two half-length transforms per column, one column per block (the
+// plain arithmetic keeps the single transform's rounding).
+template <typename R, int LOG, int DIR, int KIND, bool EXACT>
+hipError_t launch_cols_highfreq_kind(const DevPlan& P, hipStream_t s) {
+    if constexpr (LOG == 13 && KIND != kKindQuadraticPlain && KIND != kKindMixedPlain) {
+        PHI_LAUNCH((k_cols_highfreq_halves<R, LOG, DIR, KIND, EXACT>), dim3(P.n_fine / 2 + 1),
+                   dim3(FftShape<LOG>::NT / 2), 0, s, P);
+    } else {
+        constexpr int G = lines_per_block<LOG>();
+        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, KIND, EXACT>), dim3((P.n_fine / 2 + 1 + G - 1) / G),
+                   dim3(FftShape<LOG>::NT * G), 0, s, P);
+    }
+    return hipGetLastError();
+}
+
 template <typename R, int LOG, int DIR>
 hipError_t launch_cols_highfreq_dir(const DevPlan& P, hipStream_t s) {
-    constexpr int G = lines_per_block<LOG>();
-    constexpr int block = FftShape<LOG>::NT * G;
-    const int items = (P.n_fine / 2 + 1 + G - 1) / G;
-    const int grid = items;   // one work item per block
     // the exact-bounds variants are taken wherever the batched kernels take them
     // (the DS, y and mixed multipliers), so a batch member and its single plan
     // run the same code; the Coulomb multipliers use the general bounds only
     const bool exact = 2 * P.n == P.n_fine;
     if constexpr (sizeof(R) == 4 && DIR < 0) {
-        if (P.plain) {
-            if (P.component == 2 && exact)
-                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixedPlain, true>), dim3(grid), dim3(block), 0, s, P);
-            else if (P.component == 2)
-                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixedPlain, false>), dim3(grid), dim3(block), 0, s, P);
-            else if (exact)
-                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindQuadraticPlain, true>), dim3(grid), dim3(block), 0, s, P);
-            else
-                PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindQuadraticPlain, false>), dim3(grid), dim3(block), 0, s, P);
-            return hipGetLastError();
-        }
+        if (P.plain && P.component == 2)
+            return exact ? launch_cols_highfreq_kind<R, LOG, DIR, kKindMixedPlain, true>(P, s)
+                         : launch_cols_highfreq_kind<R, LOG, DIR, kKindMixedPlain, false>(P, s);
+        if (P.plain)
+            return exact ? launch_cols_highfreq_kind<R, LOG, DIR, kKindQuadraticPlain, true>(P, s)
+                         : launch_cols_highfreq_kind<R, LOG, DIR, kKindQuadraticPlain, false>(P, s);
     }
-    if (P.component == 2 && exact)
-        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixed, true>), dim3(grid), dim3(block), 0, s, P);
-    else if (P.component == 2)
-        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindMixed, false>), dim3(grid), dim3(block), 0, s, P);
-    else if (P.component == 3 && P.partition_erfc)
-        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindCoulombErfc, false>), dim3(grid), dim3(block), 0, s, P);
-    else if (P.component == 3)
-        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindCoulombGauss, false>), dim3(grid), dim3(block), 0, s, P);
-    else if (exact)
-        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindQuadratic, true>), dim3(grid), dim3(block), 0, s, P);
-    else
-        PHI_LAUNCH((k_cols_highfreq<R, LOG, DIR, kKindQuadratic, false>), dim3(grid), dim3(block), 0, s, P);
-    return hipGetLastError();
+    if (P.component == 2 && exact) return launch_cols_highfreq_kind<R, LOG, DIR, kKindMixed, true>(P, s);
+    if (P.component == 2) return launch_cols_highfreq_kind<R, LOG, DIR, kKindMixed, false>(P, s);
+    if (P.component == 3 && P.partition_erfc)
+        return launch_cols_highfreq_kind<R, LOG, DIR, kKindCoulombErfc, false>(P, s);
+    if (P.component == 3) return launch_cols_highfreq_kind<R, LOG, DIR, kKindCoulombGauss, false>(P, s);
+    if (exact) return launch_cols_highfreq_kind<R, LOG, DIR, kKindQuadratic, true>(P, s);
+    return launch_cols_highfreq_kind<R, LOG, DIR, kKindQuadratic, false>(P, s);
 }
 
 template <typename R, int LOG>
