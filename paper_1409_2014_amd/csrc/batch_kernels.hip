@@ -175,14 +175,16 @@ template <typename R, int DIR>
 hipError_t enqueue_batch_dir(const BatchDev& B, const StreamSet& ss, const void* in, void* out, hipStream_t s,
                              KernelTimer* timer) {
     const dim3 blk(kBatchThreads);
+    const bool attach = ss.side && attaches_events(s, timer);
     PHI_LAUNCH_B("rows_forward", B.n_rows, s,
                  PHI_LAUNCH((kb_rows_forward<R, DIR>), dim3(B.n_rows), blk, 0, s, B,
                                     static_cast<const R*>(in)));
+    KernelEnd fork(ss.fork, s, attach);
     PHI_LAUNCH_B("cols_type2", B.n_cols_t2, s,
                  PHI_LAUNCH((kb_cols<R, DIR, false>), dim3(B.n_cols_t2), blk, 0, s, B, B.cols_t2));
     hipStream_t side = ss.side ? ss.side : s;
     if (ss.side) {
-        PHI_TRY_B(hipEventRecord(ss.fork, s));
+        PHI_TRY_B(fork.close());
         PHI_TRY_B(hipStreamWaitEvent(side, ss.fork, 0));
     }
     PHI_LAUNCH_B("nodes", B.n_nodes, side, PHI_LAUNCH((kb_nodes_group<R>), dim3(B.n_nodes), blk, 0, side, B));
@@ -192,9 +194,10 @@ hipError_t enqueue_batch_dir(const BatchDev& B, const StreamSet& ss, const void*
     else
         PHI_LAUNCH_B("nodes", B.n_nodes_gen, side,
                      PHI_LAUNCH((kb_nodes<R, kMaxEsWidth>), dim3(B.n_nodes_gen), blk, 0, side, B));
+    KernelEnd join(ss.join, side, attach);
     PHI_LAUNCH_B("cols_type1", B.n_cols1, side,
                  PHI_LAUNCH((kb_cols_type1<R, -DIR>), dim3(B.n_cols1), blk, 0, side, B));
-    if (ss.side) PHI_TRY_B(hipEventRecord(ss.join, side));
+    if (ss.side) PHI_TRY_B(join.close());
     PHI_LAUNCH_B("cols", B.n_cols, s,
                  PHI_LAUNCH((kb_cols<R, DIR, false>), dim3(B.n_cols), blk, 0, s, B, B.cols));
     PHI_LAUNCH_B("cols_mixed", B.n_cols_mixed, s,

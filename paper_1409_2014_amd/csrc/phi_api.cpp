@@ -248,6 +248,10 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
     // 96.5..97 against 100.3, 2048^2 FP64 143..145 against 152.
     d->shared = (!hp.two_streams && hp.width <= phi::kMaxEsWidth && hp.log_fine >= phi::kSharedMinLogFine &&
                  (hp.log_fine <= 10 || (dtype == PHI_F32 && hp.log_fine <= 11))) ? 1 : 0;
+    // Where the node-side chain comes first (1024^2 FP64), a fork and a join cost an
+    // eager solve more than the overlap gives: 600^2 FP64 63.1 us on two streams, 60.3
+    // on one, 1024^2 67.0 and 62.6 (in a graph 54.3 and 55.2 on two).
+    d->serial = !hp.two_streams && hp.half.grouped && !d->highfreq_first ? 1 : 0;
     d->freq_scale = 1.0 / (f * hp.h * hp.sigma);
     d->col_stride = static_cast<int>(column_stride(hp));
     d->h2 = hp.h * hp.h;

@@ -406,6 +406,8 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
     const int dir = adjoint ? 1 : -1;
     switch (stage) {
         case Stage::Solve: {
+            const bool eager = !P.shared && ss.side && attaches_events(s, timer);
+            KernelEnd fork(ss.fork, s, eager && !P.serial);
             PHI_STEP("rows_forward", s, (run_rows_forward<R>(P, in, dir, s)));
             if (P.shared) {
                 PHI_STEP("cols_type2", s, (run_cols_type2<R>(P, dir, s)));
@@ -414,9 +416,10 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
                 PHI_STEP("rows_inverse", s, (run_rows_inverse<R>(P, out, -dir, 1, 1, s)));
                 return hipSuccess;
             }
-            hipStream_t side = ss.side ? ss.side : s;
-            if (ss.side) {
-                PHI_TRY(hipEventRecord(ss.fork, s));
+            const bool two = ss.side && !(eager && P.serial);
+            hipStream_t side = two ? ss.side : s;
+            if (two) {
+                PHI_TRY(fork.close());
                 PHI_TRY(hipStreamWaitEvent(side, ss.fork, 0));
             }
             // the branch enqueued first is served first by the dispatcher (the
@@ -424,10 +427,11 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
             if (P.highfreq_first) PHI_STEP("cols_highfreq", s, (run_cols_highfreq<R>(P, dir, s)));
             PHI_STEP("cols_type2", side, (run_cols_type2<R>(P, dir, side)));
             PHI_STEP("nodes", side, (run_nodes<R, 0>(P, nullptr, nullptr, side)));
+            KernelEnd join(ss.join, side, two && eager);
             PHI_STEP("cols_type1", side, (run_cols_type1<R>(P, -dir, side)));
-            if (ss.side) PHI_TRY(hipEventRecord(ss.join, side));
+            if (two) PHI_TRY(join.close());
             if (!P.highfreq_first) PHI_STEP("cols_highfreq", s, (run_cols_highfreq<R>(P, dir, s)));
-            if (ss.side) PHI_TRY(hipStreamWaitEvent(s, ss.join, 0));
+            if (two) PHI_TRY(hipStreamWaitEvent(s, ss.join, 0));
             PHI_STEP("rows_inverse", s, (run_rows_inverse<R>(P, out, -dir, 1, 1, s)));
             return hipSuccess;
         }
@@ -462,6 +466,16 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
 LaunchEvents& launch_events() {
     static thread_local LaunchEvents ev;
     return ev;
+}
+
+bool attaches_events(hipStream_t s, const KernelTimer* timer) {
+    if (timer) return false;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
 }
 
 hipError_t mark_kernel(KernelTimer* t, const char* name, bool end, hipStream_t s) {
