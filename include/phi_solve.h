@@ -93,7 +93,9 @@ typedef enum { PHI_F64 = 0, PHI_F32 = 1 } phi_dtype;
                                 type-1 window columns and every I1 column in one launch.  Results
                                 are bit-identical in both layouts.
                                 Larger sides and the Gaussian kernel above 16 cells always use
-                                the two-stream layout. */
+                                the two-stream layout; an eager FP64 solve of padded side 2048
+                                queues that layout's launches on the solve's stream unless this
+                                flag is set. */
 #define PHI_AUTOTUNE 2u      /* phi_plan / phi_plan_batch time the candidate bin sides {4, 8, 16} and
                                 subproblem sizes {32, 64} on the device and keep the fastest; the
                                 choice is visible in phi_plan_info.bin / .sub_nodes.  Results of

@@ -244,8 +244,8 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
     // there varies from run to run).  Splitting the I1 columns over the three
     // chain launches instead was slower at every size (e.g. 512^2 FP64 50.7,
     // 1024^2 FP32 50.1).  Where the I1 columns are the longer branch the
-    // two-stream layout is faster: 1024^2 FP64 60..63 against 63.3, 2048^2 FP32
-    // 96.5..97 against 100.3, 2048^2 FP64 143..145 against 152.
+    // two-stream layout is faster in a graph: 1024^2 FP64 55.2 against 56.8, 2048^2
+    // FP32 76.3 against 79.5, 2048^2 FP64 117.9 against 124.6.
     d->shared = (!hp.two_streams && hp.width <= phi::kMaxEsWidth && hp.log_fine >= phi::kSharedMinLogFine &&
                  (hp.log_fine <= 10 || (dtype == PHI_F32 && hp.log_fine <= 11))) ? 1 : 0;
     // Where the node-side chain comes first (1024^2 FP64), a fork and a join cost an

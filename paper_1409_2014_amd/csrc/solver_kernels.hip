@@ -7,19 +7,22 @@
 // A solve runs six kernels; the node-side chain runs on a second stream
 // concurrently with the I1 column pass:
 //
-//   rows_forward   per grid row: z = rho + i rho d(n1) d(n2) at centred
+//   rows_forward   per grid row (long rows in pairs, one transform for two): z = rho + i rho d(n1) d(n2) at centred
 //                  positions, one F-point FFT; the transform of the real part
 //                  on m = 0..F/2 (I1 half spectrum) goes to the column-major XT,
 //                  that of the imaginary part on the Q window frequencies (the
 //                  type-2 row window) to TT.   [Sec. 2.1 eq. (9); Sec. 2.2 eq. (16)]
 //   cols_highfreq  per spectrum column: F-point FFT, times g1(k)/F^2, inverse
-//                  FFT, the N centred rows back into XT.            [eq. (9)]
+//                  FFT, the N centred rows back into XT (F = 8192 in two
+//                  half-length parts).                              [eq. (9)]
 //   side stream:
 //   cols_type2     per window column of TT: F-point FFT, the Q window rows -> WIN.
-//   nodes          per subproblem (<= 64 nodes of one bin): stage the window
-//                  tile and the nodes' precomputed kernel taps in LDS,
-//                  interpolate c_j, a_j = q_j h^2 c_j, spread the a_j into the
-//                  subproblem's own tile (no atomics).  [eq. (12), (15), (16)]
+//   nodes          per subproblem (<= 64 nodes of one bin, the nodes of one half
+//                  plane in a solve): interpolate c_j from the window tile with
+//                  the nodes' precomputed kernel taps, a_j = q_j h^2 c_j, spread
+//                  the a_j into the subproblem's own tile (no atomics), on FP64
+//                  matrix instructions where the tile fits 16 x 16.
+//                  [eq. (12), (15), (16)]
 //   cols_type1     per window column: sum the tile entries of each cell in a
 //                  fixed order, F-point FFT (only the Q window inputs are
 //                  non-zero), the N centred rows times d(n2) -> U.
