@@ -145,8 +145,9 @@ WorkParts layout_work(const phi::HostPlan& hp, size_t es, Layout& L) {
     w.tt = L.take(q * cs * 2 * es);
     w.win = L.take(q * q * 2 * es);
     w.pts = L.take(m * 2 * es);
-    w.tiles = L.take(std::max(static_cast<size_t>(hp.n_sub) * hp.tile_cells,
-                              static_cast<size_t>(hp.half.n_sub) * hp.half.tile_cells) * 2 * es);
+    // both node sets store E x E tiles, and the half plane has no more of them: each
+    // of its subproblem runs is cut from a subset of one bin's nodes
+    w.tiles = L.take(static_cast<size_t>(hp.n_sub) * hp.tile * hp.tile * 2 * es);
     w.u = L.take(n * q * 2 * es);
     return w;
 }

@@ -530,8 +530,7 @@ void build_node_set(const HostPlan& hp, const std::vector<double>& kx, const std
     // window cell <- tile entries: every tile cell inside the box its nodes' taps
     // can reach, mapped to its window cell (wrapped when the window is periodic);
     // the lists are in subproblem order (two passes: count, then place)
-    const int E = grouped ? kNodeGroup : hp.tile;      // tile row length
-    set->tile_cells = E * E;
+    const int E = hp.tile;
     auto each_entry = [&](auto&& visit) {
         for (int sidx = 0; sidx < set->n_sub; ++sidx) {
             const int bx = set->sub[4 * sidx], by = set->sub[4 * sidx + 1];

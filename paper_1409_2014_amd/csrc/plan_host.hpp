@@ -40,9 +40,8 @@ struct NodeSet {
     // grouped: the set is laid out for the matrix-instruction node kernel.  Every
     // subproblem is padded to whole groups of 16 nodes (weight 0, taps 0), taps is
     // [slots][2][16] with each node's taps at their place in the tile's 16 columns
-    // (x) and rows (y), tiles are 16 x 16; kx, ky and cell are empty.
+    // (x) and rows (y); kx, ky and cell are empty.
     bool grouped = false;
-    int tile_cells = 0;                 // entries of one subproblem's tile
     // reduction of the subproblem tiles onto the window: for window cell c = x * patch + y,
     // entries contrib_start[c] .. contrib_start[c+1]-1 of contrib hold flat tile indices
     std::vector<int32_t> contrib_start, contrib;

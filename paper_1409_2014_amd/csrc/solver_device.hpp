@@ -942,8 +942,12 @@ __device__ __forceinline__ void nodes_group_body(const DevPlan& P, int sidx, Nod
         v_re += s.part[wv][0][c];
         v_im += s.part[wv][1][c];
     }
-    static_cast<cpx<R>*>(P.tiles)[static_cast<size_t>(sidx) * T * T + c] = {static_cast<R>(v_re),
-                                                                           static_cast<R>(v_im)};
+    // the E x E cells the taps reach, as the general kernel stores them: 16 x 16 ones
+    // would outgrow the workspace the general kernel needs
+    const int E = P.tile, cb = c / T, ca = c % T;
+    if (cb < E && ca < E)
+        static_cast<cpx<R>*>(P.tiles)[static_cast<size_t>(sidx) * E * E + cb * E + ca] = {static_cast<R>(v_re),
+                                                                                         static_cast<R>(v_im)};
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,24 @@
+"""Tile storage of the half-plane node set, checked in the plan construction code
+(CPU C++): at small kernel widths, small subproblems and node counts whose
+workspace is near the static scratch's size."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+CSRC = os.path.join(ROOT, "paper_1409_2014_amd", "csrc")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
+def test_half_plane_tiles_fit_the_workspace(tmp_path):
+    exe = tmp_path / "tile_storage_driver"
+    cmd = ["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", f"-I{ROOT}/include", f"-I{CSRC}", "-I/opt/rocm/include",
+           os.path.join(ROOT, "tests", "host", "tile_storage_driver.cpp"), os.path.join(CSRC, "plan_host.cpp"),
+           "-o", str(exe)]
+    build = subprocess.run(cmd, capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-2000:]
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stdout[-2000:]
