@@ -101,6 +101,7 @@ struct NodeParts {
 struct TableParts {
     Part delta, deconv, gx, gy, gyr, twr, twn;
     NodeParts half, all;
+    bool all_nodes = true;
 };
 // everything a solve writes
 struct WorkParts {
@@ -118,8 +119,11 @@ NodeParts layout_nodes(const phi::NodeSet& ns, size_t es, Layout& L) {
     return t;
 }
 
-TableParts layout_tables(const phi::HostPlan& hp, size_t es, Layout& L) {
+// all_nodes: with the full node set, which the type-2 and type-1 stages and the
+// plain solve read; batches take none of them.
+TableParts layout_tables(const phi::HostPlan& hp, size_t es, bool all_nodes, Layout& L) {
     TableParts t;
+    t.all_nodes = all_nodes;
     const size_t n = hp.n, f = hp.n_fine;
     t.delta = L.take(hp.delta.size() * 8);
     t.deconv = L.take(n * 8);
@@ -127,7 +131,7 @@ TableParts layout_tables(const phi::HostPlan& hp, size_t es, Layout& L) {
     t.gy = L.take(2 * f * 8);
     t.gyr = L.take(2 * f * es);
     t.half = layout_nodes(hp.half, es, L);
-    t.all = layout_nodes(hp, es, L);
+    if (all_nodes) t.all = layout_nodes(hp, es, L);
     t.twr = L.take(hp.twr.size() * es);
     t.twn = L.take(hp.twn.size() * es);
     return t;
@@ -182,7 +186,7 @@ hipError_t upload_tables(const phi::HostPlan& hp, const TableParts& t, char* bas
         if (e == hipSuccess) e = up(np.taps, narrow(ns.taps));
     };
     up_nodes(t.half, hp.half);
-    up_nodes(t.all, hp);
+    if (t.all_nodes) up_nodes(t.all, hp);
     const void* twr = hp.twr.data();
     if (f32) {
         keep.emplace_back();
@@ -278,7 +282,7 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
         return nt;
     };
     d->nd = tables(t.half, hp.half);
-    d->nd_all = tables(t.all, hp);
+    d->nd_all = t.all_nodes ? tables(t.all, hp) : d->nd;
     d->bin = hp.bin;
     d->tile = hp.tile;
     d->twr = base + t.twr.off;
@@ -330,7 +334,7 @@ phi_status create_single(const phi_params* p, hipStream_t s, phi_plan_s** out) {
     const bool f32 = (p->dtype == PHI_F32);
     const size_t es = f32 ? 4 : 8;
     Layout L;
-    const TableParts tp = layout_tables(hp, es, L);
+    const TableParts tp = layout_tables(hp, es, true, L);
     const WorkParts wp = layout_work(hp, es, L);
     plan->block_bytes = L.cursor;
     e = hipMalloc(&plan->block, L.cursor);
@@ -660,7 +664,7 @@ phi_status phi_plan_batch(const phi_params* members, int32_t count, void* stream
         // one allocation: table sets, member workspaces, device views, work tables
         Layout L;
         std::vector<TableParts> tparts;
-        for (const phi::HostPlan& hp : plan->sets) tparts.push_back(layout_tables(hp, es, L));
+        for (const phi::HostPlan& hp : plan->sets) tparts.push_back(layout_tables(hp, es, false, L));
         std::vector<WorkParts> wparts;
         for (int i = 0; i < count; ++i) wparts.push_back(layout_work(plan->sets[plan->member_set[i]], es, L));
         const Part p_dev = L.take(sizeof(phi::DevPlan) * count);

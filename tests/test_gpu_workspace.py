@@ -29,3 +29,23 @@ def test_noalloc_takes_plans_near_the_scratch_size(n, dtype, kw):
     torch.cuda.synchronize()
     plan.close()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_batch_plans_hold_no_tables_of_the_stage_entry_points(dtype):
+    """A batch takes solves only, so next to a single plan of the same problem it
+    lacks at least the taps of the full node set (2 w values per node); its work
+    lists and member views are under 64 KiB here."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1409_2014_amd as ps
+    print(f"case: batch plan memory {dtype}", flush=True)
+    member = dict(n=256, h=1.0 / 16, n_r=128, n_theta=256)
+    plan, batch = ps.Plan(**member, dtype=dtype), ps.BatchPlan([member], dtype=dtype)
+    taps = plan.info["n_nodes"] * 2 * plan.info["kernel_width"] * (4 if dtype == torch.float32 else 8)
+    sizes = plan.info["device_bytes"], batch.device_bytes
+    rho = torch.rand((256, 256), dtype=dtype, device="cuda")
+    assert torch.equal(batch.solve(rho.reshape(-1)).view(256, 256), plan.solve(rho))
+    plan.close()
+    batch.close()
+    assert sizes[1] <= sizes[0] - taps + 65536, sizes
