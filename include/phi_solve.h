@@ -94,8 +94,8 @@ typedef enum { PHI_F64 = 0, PHI_F32 = 1 } phi_dtype;
                                 are bit-identical in both layouts.
                                 Larger sides and the Gaussian kernel above 16 cells always use
                                 the two-stream layout; an eager FP64 solve of padded side 2048
-                                queues that layout's launches on the solve's stream unless this
-                                flag is set. */
+                                whose spread tile (bin + w - 1) is at most 16 cells queues that
+                                layout's launches on the solve's stream unless this flag is set. */
 #define PHI_AUTOTUNE 2u      /* phi_plan / phi_plan_batch time the candidate bin sides {4, 8, 16} and
                                 subproblem sizes {32, 64} on the device and keep the fastest; the
                                 choice is visible in phi_plan_info.bin / .sub_nodes.  Results of
@@ -239,9 +239,9 @@ phi_status phi_solve_periodic(phi_plan_t plan, const void* rho, void* phi, void*
 phi_status phi_solve_highfreq(phi_plan_t plan, const void* rho, void* i1, void* stream);
 phi_status phi_solve_lowfreq(phi_plan_t plan, const void* rho, void* i2, void* stream);
 
-/* Measurement only: enqueues the same kernels as phi_solve (adjoint = 0) or
- * phi_solve_adjoint (adjoint = 1) with a HIP event recorded on `stream` before
- * each kernel and after the last, then waits for the stream.  Writes the
+/* Measurement only: enqueues the same kernels, on the same streams, as an eager
+ * phi_solve (adjoint = 0) or phi_solve_adjoint (adjoint = 1), each launched with a
+ * start and a stop event, then waits for the stream.  Writes the
  * number of kernels to *count and, for i < min(*count, capacity), the i-th
  * kernel's duration in milliseconds to kernel_ms[i] and its name (a static
  * string owned by the library) to names[i].  Unlike phi_solve it blocks the

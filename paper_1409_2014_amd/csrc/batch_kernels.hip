@@ -175,7 +175,7 @@ template <typename R, int DIR>
 hipError_t enqueue_batch_dir(const BatchDev& B, const StreamSet& ss, const void* in, void* out, hipStream_t s,
                              KernelTimer* timer) {
     const dim3 blk(kBatchThreads);
-    const bool attach = ss.side && attaches_events(s, timer);
+    const bool attach = ss.side && !timer && is_eager(s);
     PHI_LAUNCH_B("rows_forward", B.n_rows, s,
                  PHI_LAUNCH((kb_rows_forward<R, DIR>), dim3(B.n_rows), blk, 0, s, B,
                                     static_cast<const R*>(in)));

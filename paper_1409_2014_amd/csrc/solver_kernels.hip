@@ -409,8 +409,11 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
     const int dir = adjoint ? 1 : -1;
     switch (stage) {
         case Stage::Solve: {
-            const bool eager = !P.shared && ss.side && attaches_events(s, timer);
-            KernelEnd fork(ss.fork, s, eager && !P.serial);
+            // the layout is the stream's and the plan's: a timed solve runs the one it times
+            const bool eager = !P.shared && ss.side && is_eager(s);
+            const bool two = ss.side && !(eager && P.serial);
+            const bool attach = eager && two && !timer;    // a timed launch carries the timer's events
+            KernelEnd fork(ss.fork, s, attach);
             PHI_STEP("rows_forward", s, (run_rows_forward<R>(P, in, dir, s)));
             if (P.shared) {
                 PHI_STEP("cols_type2", s, (run_cols_type2<R>(P, dir, s)));
@@ -419,7 +422,6 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
                 PHI_STEP("rows_inverse", s, (run_rows_inverse<R>(P, out, -dir, 1, 1, s)));
                 return hipSuccess;
             }
-            const bool two = ss.side && !(eager && P.serial);
             hipStream_t side = two ? ss.side : s;
             if (two) {
                 PHI_TRY(fork.close());
@@ -430,7 +432,7 @@ hipError_t enqueue_typed(const DevPlan& plan, const StreamSet& ss, Stage stage, 
             if (P.highfreq_first) PHI_STEP("cols_highfreq", s, (run_cols_highfreq<R>(P, dir, s)));
             PHI_STEP("cols_type2", side, (run_cols_type2<R>(P, dir, side)));
             PHI_STEP("nodes", side, (run_nodes<R, 0>(P, nullptr, nullptr, side)));
-            KernelEnd join(ss.join, side, two && eager);
+            KernelEnd join(ss.join, side, attach);
             PHI_STEP("cols_type1", side, (run_cols_type1<R>(P, -dir, side)));
             if (two) PHI_TRY(join.close());
             if (!P.highfreq_first) PHI_STEP("cols_highfreq", s, (run_cols_highfreq<R>(P, dir, s)));
@@ -471,8 +473,7 @@ LaunchEvents& launch_events() {
     return ev;
 }
 
-bool attaches_events(hipStream_t s, const KernelTimer* timer) {
-    if (timer) return false;
+bool is_eager(hipStream_t s) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &status) != hipSuccess) {
         (void)hipGetLastError();

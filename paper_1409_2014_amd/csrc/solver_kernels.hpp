@@ -138,9 +138,10 @@ private:
     bool attach_;
 };
 
-// Whether launches on s can carry such an event: not while they are timed (the timer
-// has the events) and not under capture (a graph takes the record as its edge).
-bool attaches_events(hipStream_t s, const KernelTimer* timer);
+// Whether work queued on s runs at once, and its launches can carry such an event
+// (false under capture, where a graph takes the record as its edge, and where the
+// stream cannot be asked).
+bool is_eager(hipStream_t s);
 
 // Padded sides (log2) for which the one-stream layout's kernel is built.
 constexpr int kSharedMinLogFine = 4;
