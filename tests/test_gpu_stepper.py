@@ -424,3 +424,34 @@ def test_full_size_run_invariants(ps, dtype, mass_bar):
         print(f"FD {fd:.10e} adjoint {dot:.10e}", flush=True)
         assert abs(fd - dot) <= 1e-6 * abs(dot)
     st.close()
+
+
+@pytest.mark.parametrize("n,half,scheme", [(128, 8.0, "strang"), (256, 8.0, "yoshida4"), (1024, 16.0, "strang")])
+def test_fp32_losses_and_gradients_of_every_route_agree(ps, n, half, scheme):
+    """J and dJ/du0 in FP32 by loss_and_grad (whose runs are phi_ds_forward_plain's), by
+    ds_evolve, and J by forward and moments over the same segments.  The last two are
+    the same calls and give the same field (one call over all steps does not: it
+    merges the linear substeps between two segments).  Between them and loss_and_grad
+    the trajectories differ by rounding: a rotation by its sine and cosine, 2^-24
+    each, and the potential's 1e-6 times a phase of 1e-2 at most, per substep; J goes
+    with the fourth power of the field."""
+    print(f"case: FP32 routes to a loss N={n} {scheme}", flush=True)
+    steps = 6
+    st = ps.DSStepper(n, 2 * half / n, tau=1e-3, dtype=torch.float32, scheme=scheme, tol=1e-7)
+    u0 = dev(initial(n, half, kx=0.5), torch.float32)
+    loss, g, _ = st.loss_and_grad(u0, steps, checkpoint_every=2)
+    x = u0.clone().requires_grad_(True)
+    u_t = ps.ds_evolve(x, st, steps, 2)
+    ((2 * half / n) ** 2 * torch.sum(torch.abs(u_t) ** 4)).backward()
+    u = u0.clone()
+    for m in st.segments(steps, 2):
+        st.forward(u, m)
+    j = st.moments(u)[1]
+    assert torch.equal(u_t.detach(), u)
+    err = abs(float(j) - float(loss)) / float(loss)
+    gerr = float((x.grad - g).norm() / g.norm())
+    st.close()
+    per_substep = 4 * (2 * 2.0 ** -24 + 1e-6 * 1e-2)
+    bar = per_substep * steps * st.substeps
+    print(f"  loss {err:.2e} (bar {bar:.1e}), gradient {gerr:.2e} (bar {4 * bar:.1e})", flush=True)
+    assert err <= bar and gerr <= 4 * bar
