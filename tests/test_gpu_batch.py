@@ -242,3 +242,21 @@ def test_batch_argument_errors(ps):
     assert B.STATUS_NAMES[st] == "PHI_ERR_UNSUPPORTED"
     assert bp.offsets == [0, 128 * 128, 2 * 128 * 128]
     bp.close()
+
+
+def test_ragged_members_above_1024_fp64(ps):
+    """Members whose rows run in pairs next to members whose rows do not: bitwise
+    equal to their single plans, forward and transposed."""
+    sizes = [1026, 130, 1500, 700]
+    members = member_list(len(sizes), seed=31, sizes=sizes)
+    dtype = torch.float64
+    print(f"case: ragged batch {sizes} {dtype}", flush=True)
+    bp = ps.BatchPlan(batch_params(members, dtype), dtype=dtype)
+    packed = bp.pack([m[2] for m in members])
+    used = [t.double().cpu().numpy() for t in bp.unpack(packed)]
+    for adjoint in (False, True):
+        out = (bp.solve_adjoint if adjoint else bp.solve)(packed)
+        single = single_solves(ps, members, dtype, adjoint=adjoint, inputs=used)
+        for i, t in enumerate(bp.unpack(out)):
+            assert np.array_equal(t.cpu().numpy(), single[i]), f"member {i} (N={sizes[i]})"
+    bp.close()

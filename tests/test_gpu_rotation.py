@@ -68,3 +68,25 @@ def test_a_phase_that_is_not_a_number_stays_one(dtype):
     torch.cuda.synchronize()
     st.close()
     assert bool(torch.isnan(torch.view_as_real(out)).any())
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("phase", [0.3, 9.9e5, 1.0e6, 1.5e6, 3.1e7])
+def test_rotation_of_a_constant_field(dtype, phase):
+    """A constant field of size 1/2 goes through the transforms exactly (sums of equal
+    values, the zero mode's factors are 1) and its periodic potential is 0, so a step
+    multiplies it by e^{i phase} alone, on either side of the branch-free range (1e6)
+    and at its edge.  The phase is the product of two rounded numbers; the sine and
+    cosine are within 4 ulps of 1, and the products of the field add rounding."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1409_2014_amd as ps
+    print(f"case: rotation of a constant field {dtype} phase {phase}", flush=True)
+    real = np.float64 if dtype == torch.float64 else np.float32
+    tau, c = 2.0 ** -10, 4.0 * phase * 2.0 ** 10       # |u|^2 = 1/4; tau and |u|^2 are exact
+    st = ps.DSStepper(64, 0.25, dtype=dtype, tau=tau, potential="periodic", c_local=c, c_potential=c)
+    u = torch.full((64, 64), 0.5, dtype=CDT[dtype], device="cuda")
+    got = st.forward(u, 1).cpu().numpy()
+    st.close()
+    want = 0.5 * np.exp(1j * float(real(c) * real(0.25) * real(tau)))
+    assert np.max(np.abs(got - want)) <= 8 * EPS[dtype]

@@ -71,3 +71,18 @@ def test_queued_batches_equal_replays(dtype):
     for got, ref in zip(sequence(plan.solve, inputs, torch.cuda.Stream()), want):
         assert torch.equal(got, ref)
     plan.close()
+
+
+@pytest.mark.parametrize("n,dtype", [(64, torch.float64), (1024, torch.float64), (2048, torch.float32),
+                                     (2050, torch.float32)])
+def test_queued_transposed_solves_equal_replays(n, dtype):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1409_2014_amd as ps
+    print(f"case: queued transposed solves N={n} {dtype}", flush=True)
+    plan = ps.Plan(n, 16.0 / n, dtype=dtype)
+    inputs = inputs_like((n, n), dtype)
+    want = replayed(plan.solve_adjoint, inputs)
+    for got, ref in zip(sequence(plan.solve_adjoint, inputs, torch.cuda.Stream()), want):
+        assert torch.equal(got, ref)
+    plan.close()
