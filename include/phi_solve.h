@@ -113,7 +113,10 @@ typedef struct {
     double hx, hy;         /* spacings; must be equal and > 0; box side = n h, centred at 0     */
     int32_t n_r;           /* radial Gauss-Legendre nodes, 1..1024                              */
     int32_t n_theta;       /* azimuthal trapezoid nodes, even, 2..4096                          */
-    double tol;            /* NUFFT relative accuracy: F64 [1e-15, 1e-1], F32 [1e-7, 1e-1]      */
+    double tol;            /* NUFFT relative accuracy: F64 [1e-15, 1e-1], F32 [1e-7, 1e-1].  From
+                              F = 2048 (F32) and 4096 (F64) on, the kernel's deconvolution along x
+                              is a short series within tol / 100 of the exact factors (at best
+                              1e-9, 1.5e-15) where one is found                                   */
     int32_t pad;           /* zero-padding factor kappa of the I1 box, 2..8 (0: 2).  The padded
                               box (Sec. 2.1, kappa >= 2) has the side F = the smallest power of
                               two >= kappa N; F is also the NUFFT fine grid (oversampling F/N)  */
@@ -128,7 +131,11 @@ typedef struct {
     int32_t sub_nodes;     /* most nodes per spreading / interpolation block, 8..64 (0: 64)      */
 } phi_params;
 
-/* Derived quantities of a plan (filled by phi_describe / phi_plan_get_info). */
+/* Derived quantities of a plan (filled by phi_describe / phi_plan_get_info).
+ * max_cell_nodes, max_gather, n_sub and n_contrib are those of the full set of
+ * n_nodes nodes, which the type-2 and type-1 stages run on.  A solve runs on the
+ * nodes of one half plane (rho and the multiplier's node weights are real and even),
+ * with about half as many of each. */
 typedef struct {
     int32_t n;             /* grid side N                                        */
     int32_t n_fine;        /* FFT / fine-grid side F: smallest power of two >= kappa N */

@@ -148,7 +148,7 @@ WorkParts layout_work(const phi::HostPlan& hp, size_t es, Layout& L) {
     w.xt = L.take((f / 2 + 1) * cs * 2 * es);
     w.tt = L.take(q * cs * 2 * es);
     w.win = L.take(q * q * 2 * es);
-    w.pts = L.take(m * 2 * es);
+    w.pts = L.take(m * 2 * es);    // no kernel uses it; it is part of what phi_solve_noalloc's limit counts
     // both node sets store E x E tiles, and the half plane has no more of them: each
     // of its subproblem runs is cut from a subset of one bin's nodes
     w.tiles = L.take(static_cast<size_t>(hp.n_sub) * hp.tile * hp.tile * 2 * es);
@@ -234,28 +234,27 @@ void fill_dev(const phi::HostPlan& hp, phi_dtype dtype, char* base, const TableP
     // served first: the node-side chain (the same few small kernels at every N)
     // unless the high-frequency columns carry at least the work they have in a
     // 2048^2 FP32 solve (N F log2 F times the element size), where they are the
-    // longer branch.  Graph replay on MI355X: 2048^2 FP32 98.2 -> 95.8..97.2 us
-    // with the columns first, 1024^2 FP64 60.5 -> 70.5 us (so chain first there).
+    // longer branch.  Graph replay on MI355X, columns first / chain first: 2048^2 FP32
+    // 77.0 / 81.5 us, 2048^2 FP64 119.0 / 127.2, 1024^2 FP64 64.8 / 55.8.
     const double col_work = (f / 2) * f * std::log2(f) * (dtype == PHI_F32 ? 4.0 : 8.0);
     d->highfreq_first = col_work >= 2048.0 * 4096.0 * 12.0 * 4.0 ? 1 : 0;
     // Padded sides up to 1024 (both precisions) and FP32 solves on padded side
     // 2048 run the one-stream layout: cols_type2, nodes, then the type-1 window
-    // columns and every I1 column in one launch.  Graph replay on MI355X, two
-    // runs each (µs): 64^2 FP64 42.5, 43.4 -> 36.3, 36.2; 128^2 FP64 44.9, 51.4
-    // -> 37.7, 37.6; 256^2 FP32 51.5, 45.1 -> 36.7, 36.8; 256^2 FP64 48.4, 50.9 ->
-    // 41.1, 41.0 (against the one launch with device-counter waits that these
-    // sides used before); 512^2 FP32 63.7 -> 38.8, 512^2 FP64 52.5..71 -> 44.8;
-    // 1024^2 FP32 49..58 -> 48.6 (against the two-stream layout, whose time
-    // there varies from run to run).  Splitting the I1 columns over the three
-    // chain launches instead was slower at every size (e.g. 512^2 FP64 50.7,
-    // 1024^2 FP32 50.1).  Where the I1 columns are the longer branch the
-    // two-stream layout is faster in a graph: 1024^2 FP64 55.2 against 56.8, 2048^2
-    // FP32 76.3 against 79.5, 2048^2 FP64 117.9 against 124.6.
+    // columns and every I1 column in one launch.  Graph replay on MI355X, one stream /
+    // two (us; below 1024^2 the second varies from run to run): 64^2 FP32 27.9 /
+    // 31.2..44.2, FP64 30.0 / 33.7..43.0; 128^2 FP64 30.1 / 33.4..43.1; 256^2 FP32 30.3 /
+    // 33.9..43.5, FP64 32.3 / 35.5..43.3; 512^2 FP32 32.7 / 36.0..42.9, FP64 36.9 /
+    // 38.7..42.9; 1024^2 FP32 46.2 / 45.0..45.8.  Splitting the I1 columns over the three
+    // chain launches instead was slower at every size (512^2 FP64 33.4 -> 37..40).
+    // Where the I1 columns are the longer branch two streams are faster in a graph:
+    // 1024^2 FP64 60.2 / 55.7, 2048^2 FP32 82.9 / 77.1, 2048^2 FP64 128.5 / 119.0.
     d->shared = (!hp.two_streams && hp.width <= phi::kMaxEsWidth && hp.log_fine >= phi::kSharedMinLogFine &&
                  (hp.log_fine <= 10 || (dtype == PHI_F32 && hp.log_fine <= 11))) ? 1 : 0;
     // Where the node-side chain comes first (1024^2 FP64), a fork and a join cost an
-    // eager solve more than the overlap gives: 600^2 FP64 63.1 us on two streams, 60.3
-    // on one, 1024^2 67.0 and 62.6 (in a graph 54.3 and 55.2 on two).
+    // eager solve more than the overlap gives, queued behind others or alone.  On one
+    // stream / on two: 600^2 FP64 queued 59.2 / 63.5 us, waited for by itself 74.7 /
+    // 80.9; 1024^2 61.6 / 66.6 and 77.6 / 83.8.  The host's part of a call is 17.5 / 49
+    // us.  (In a graph two: 1024^2 55.8 against 60.2 with the columns in one launch.)
     d->serial = !hp.two_streams && hp.half.grouped && !d->highfreq_first ? 1 : 0;
     d->freq_scale = 1.0 / (f * hp.h * hp.sigma);
     d->col_stride = static_cast<int>(column_stride(hp));

@@ -282,9 +282,12 @@ __device__ __forceinline__ constexpr R tiny_normal() {
 // the float nearest 1/sqrt(2), 1 - 1.7e-8 (no float does better), and a quarter of
 // a radix-16 or radix-8 stage's terms pass one: the four transforms of a solve
 // lose 1.7e-8 of the amplitude per such stage, which the multiplier gives back.
-// Measured as the mean scale of a solve against float64 sums, 64^2 to 3000^2:
-// -5e-8 to -9e-8 before, within 1e-8 of 0 with it; the whole error, 1.2e-7 to
-// 2e-7, becomes that of rounding alone.  (FP64 constants lose nothing that matters.)
+// Measured as the mean scale of a solve against float64 sums, x, y and xy, 100^2 to
+// 4096^2: -1.6e-7 to +2.6e-8 with one row per transform and the tabulated quotient;
+// now +0.3e-8 to +1.7e-8 below padded side 4096, +1.7e-8 to +3.6e-8 from there on.
+// The whole relative L2 error is 1.0e-7 to 2.3e-7 either way.  The Coulomb kinds
+// go without: their mean scale is -4e-8 to +1.4e-8 as it is, and giving them the
+// same would add 3.4e-8 or 5.1e-8.  (FP64 constants lose nothing that matters.)
 template <typename R, int LOG>
 __device__ __forceinline__ constexpr R norm_loss() {
     constexpr int stages = FftShape<LOG>::S16 + (FftShape<LOG>::REM == 3 ? 1 : 0);
@@ -373,7 +376,8 @@ struct ColumnFactor {
             const R q0 = num * r;
             const R q = fma(fma(-q0, den, num), r, q0);
             const R w = fma(B, part_e, part_a);
-            return fma(q, w, (q * norm_loss<R, LOG>()) * w);   // less than half an ulp: added before rounding
+            // 0.3 (one stage) to 1.7 (three) half ulps: added before the product is rounded
+            return fma(q, w, (q * norm_loss<R, LOG>()) * w);
         } else {
             R num;
             if constexpr (KIND == kKindMixed || KIND == kKindMixedPlain) num = nyquist ? R(0) : fx * (my * fs);
