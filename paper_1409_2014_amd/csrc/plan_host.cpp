@@ -666,7 +666,8 @@ void fit_deconv_series(HostPlan* hp, double tol) {
     // most of a small plan's time); at a loose FP64 tolerance 8 or 12 would pass too, and
     // the plan takes a series that is closer than asked for
     const int first = hp->dtype == PHI_F32 ? 8 : 5 * hp->n > 2 * nf ? 24 : 16;
-    for (int taps = first; taps <= kMaxPairTaps; taps += 4) {
+    const int most = hp->log_fine == 11 ? kMaxPairTaps2048 : kMaxPairTaps;
+    for (int taps = first; taps <= most; taps += 4) {
         // frequencies the series reaches from the window must not meet their mirror image
         if (hp->patch / 2 + taps >= nf / 2) return;
         const int ns = 4 * taps, far = 2 * taps, cols = taps + 1, rows = ns + far + 1;
