@@ -24,14 +24,14 @@ constexpr int kBinSize = 4;            // default bin side in fine-grid cells (m
 constexpr int kMaxBinSize = 16;        // largest bin side
 constexpr int kMaxNodesPerSub = 64;    // most nodes per interp / spread subproblem
 constexpr int kMaxPairTaps = 32;       // longest deconvolution series of the paired row kernels
-// padded sides (log2) from which they are used
-constexpr int kPairMinLogF32 = 11, kPairMinLogF64 = 12;
-// The same at padded side 2048, where a pair has 128 threads for the convolution and
+// and at padded side 2048, where a pair has 128 threads for the convolution and
 // the rows are short: FP32 Gaussian plans at 1e-7, pairs / one row per transform:
 // 600^2 (16 terms) 49.1 / 47.3 us, 700^2 (20) 51.4 / 49.0, 900^2 (28) 54.9 / 53.9.  With
 // 8 or 12 terms pairs win or cost nothing that can be measured: ES 514^2 40.6 / 41.3,
 // 900^2 46.9 / 49.4, 1024^2 46.3 / 46.8, 1022^2 49.0 / 48.9.  (Graph replay.)
 constexpr int kMaxPairTaps2048 = 12;
+// padded sides (log2) from which they are used
+constexpr int kPairMinLogF32 = 11, kPairMinLogF64 = 12;
 constexpr int kMaxPairWindow = 64;     // and their widest window
 constexpr int kNodeGroup = 16;         // nodes per matrix-instruction group, and its padded tile side
 
