@@ -55,11 +55,11 @@ VALU_PEAK_PUBLISHED_F32 = 157.3
 # until the counters are taken again.
 TRAFFIC_RECORD = {
     "kernel": "cols_highfreq",
-    "fetch_kib": 16753.1, "write_kib": 32784.0,
-    "copy_fetch_kib": 131094.12, "copy_write_kib": 262144.0, "copy_true_kib": 262144.0,
+    "fetch_kib": 16753.07, "write_kib": 32784.0,
+    "copy_fetch_kib": 131088.5, "copy_write_kib": 262144.0, "copy_true_kib": 262144.0,
     "sources": ("device_common.hpp", "fft_reg.hpp", "solver_device.hpp", "solver_kernels.hip",
                 "solver_kernels.hpp"),
-    "sha256": "4d362ea9137a73094333c0dc4df0bbdf3c1bbdf3974e74d96d79f742a350eff0",
+    "sha256": "052593fdee155a622f539e470966ea53e25308df9f3b4929427788667de95d87",
 }
 
 N = 2048
@@ -609,6 +609,7 @@ def main() -> int:
         # the paper's split of solve time (Sec. 3): FFT-side kernels (I1, with the type-2
         # row transform and the recombination fused in) against the node-side kernels
         "time_split_f32": time_split(kernels_split),
+        # (n_sub counts the subproblems of all nodes; a solve runs those of one half plane)
         "node_sort": {"bin": plan32.info["bin"], "sub_nodes": plan32.info["sub_nodes"],
                       "n_sub": plan32.info["n_sub"]},
         # the FFT kernels are bound by their vector ALU work (the counters show
