@@ -84,9 +84,9 @@ phi_status phi_ds_forward(phi_ds_t ds, void* u, int32_t steps, void* v_store, vo
  * are the same.  Neither is nearer to an FP64 run: over 64^2 to 2048^2 the FP32 loss
  * of 5 Strang steps is 6.5e-7 to 1.6e-6 low in plain arithmetic and 5.4e-7 to 1.2e-6
  * in phi_ds_forward's, that of 20 steps 1.9e-6 to 4.0e-6 and 2.1e-6 to 3.9e-6, and the
- * gradient's error after phi_ds_forward is 0.76 to 1.05 of the plain one's.  The two losses differ by 4e-8 to
- * 4e-7; one run cut into segments of another length, whose linear substeps are then
- * not merged, moves either by 1e-7 to 2e-6. */
+ * gradient's error after phi_ds_forward is 0.76 to 1.05 of the plain one's.  The two
+ * losses differ by 4e-8 to 4e-7; one run cut into segments of another length, whose
+ * linear substeps are then not merged, moves either by 1e-7 to 2e-6. */
 phi_status phi_ds_forward_plain(phi_ds_t ds, void* u, int32_t steps, void* v_store, void* phi_store, void* stream);
 
 /* Reverse pass of `steps` steps: g holds the gradient with respect to the
